@@ -216,11 +216,11 @@ int mlbicgstab_workspace_size(const mlb_matrix* A, const mlb_options* opt, size_
 int mlbicgstab_solve(mlb_handle h, const void* b, void* x, const void* Q, int64_t ldq, mlb_result* res);
 
 /*
- * Solve `count` prepared systems in one launch, one workgroup per system: the
- * whole iteration of Algorithm 7.1 (M = I) of system k runs in workgroup k,
- * with workgroup barriers where the multi-launch solve has kernel boundaries
- * (an addition of this library, for many small systems, whose multi-launch
- * iteration is bound by launch latency rather than bandwidth).  Every h[k]
+ * Solve `count` prepared systems in one launch, a group of workgroups per system
+ * (the kernel that mlbicgstab_solve runs for a system of such a size): the whole
+ * iteration of Algorithm 7.1 (M = I) of a system runs in its group (an addition of
+ * this library, for many small systems, which one at a time leave most of the device
+ * idle).  Every h[k]
  * must come from mlbicgstab_create with a CSR matrix of at most
  * MLB_BATCH_MAX_N rows, MLB_PREC_FP64, MLB_PRECOND_NONE and MLB_ORDER_FUSED (an iterate
  * record is kept as in a solve; transpose_free handles run the transpose-free

@@ -2,14 +2,15 @@
 // the per-cycle launch schedule of Algorithm 7.1 (M = I; the block-Jacobi M is
 // folded into A M^{-1}), in the fused order, the literal order or the
 // transpose-free form, the construction of A^H, the fp32-inner /
-// fp64-refinement driver, batched one-workgroup solves, sequences of systems
-// with the choice of n of Section 5.2, and the serving loop.
+// fp64-refinement driver, whole solves in one launch (single and batched),
+// sequences of systems with the choice of n of Section 5.2, and the serving loop.
 //
 // One Engine<V> owns the Krylov workspace for one value type V (fp64 or fp32,
 // real or complex).  Every step of the iteration is a kernel from
 // mlb_kernels.hpp; the host only enqueues them, cycle by cycle, and watches a
 // host-mapped "done" flag the device raises when the solve ends.  The host
-// stays at most two cycles ahead of the device, so the iteration never waits
+// (Systems of up to some hundred thousand rows run whole in one launch instead,
+// mlb_grid.hpp.)  It stays at most two cycles ahead of the device, so the iteration never waits
 // for the host and the kernels of at most one cycle run after the end (they
 // return at once because the device flag is set).
 #include <hip/hip_ext.h>
@@ -33,7 +34,7 @@
 #include "../../include/mlbicgstab.h"
 #include "mlb_kernels.hpp"
 #include "mlb_spmv.hpp"
-#include "mlb_small.hpp"
+#include "mlb_grid.hpp"
 #include "mlb_precond.hpp"
 #include "mlb_ilu.hpp"
 #include "mlb_transpose.hpp"
@@ -550,6 +551,43 @@ __global__ void k_init_state(State<Sc>* st, double tol, long long maxit, double 
 }
 
 
+// ------------------------------------------------------------------ whole-solve launches
+
+// The workgroups of a whole-solve launch (mlb_grid.hpp) wait for each other, so
+// launches of one process share the device's workgroup slots through this gate: a
+// launch takes its share before it starts, and two of them never hold the device half
+// each, waiting.  (Other launches end by themselves; a group of another process that
+// holds slots makes the kernel leave at its own gate, and it is started again.)
+struct GridGate {
+  static constexpr int MAX_DEVICES = 64;
+  struct Dev {
+    std::mutex mu;
+    std::condition_variable cv;
+    double used = 0;
+  };
+  static Dev& dev() {
+    static Dev devs[MAX_DEVICES];
+    int d = 0;
+    (void)hipGetDevice(&d);
+    return devs[d >= 0 && d < MAX_DEVICES ? d : 0];
+  }
+  Dev& d;
+  double share;
+  explicit GridGate(double s) : d(dev()), share(std::min(s, 1.0)) {
+    std::unique_lock<std::mutex> lk(d.mu);
+    d.cv.wait(lk, [&] { return d.used + share <= 1.0 + 1e-9; });
+    d.used += share;
+  }
+  ~GridGate() {
+    {
+      std::lock_guard<std::mutex> lk(d.mu);
+      d.used -= share;
+    }
+    d.cv.notify_all();
+  }
+};
+constexpr int GRID_STARTS = 20;   // starts of a launch whose groups left at their gate
+
 // ------------------------------------------------------------------ engine
 
 template <class V>
@@ -591,6 +629,11 @@ struct Engine {
   // wider reduction costs more than the saved reads; complex n = 16 would need
   // 154 VGPRs in the alpha pass.
   bool s_alpha = false;
+  // Whole solves in one launch (mlb_grid.hpp): workgroups and rows per workgroup, 0:
+  // the multi-launch iteration.  Set by set_n.
+  int grid_P = 0, grid_R = 0, grid_cap = 0;
+  unsigned grid_max_tries = ~0u;
+  long long grid_entry_ticks = GRID_ENTRY_TICKS;
 
   // ext_flag: a pinned, host-mapped int the caller owns (serving workers reuse one
   // per worker); NULL = allocate one.
@@ -670,6 +713,71 @@ struct Engine {
       const long long rounds = (tiles + grid_spmv - 1) / grid_spmv;
       grid_spmv = (int)std::max(1LL, (tiles + rounds - 1) / rounds);
     }
+    pick_grid();
+  }
+
+  bool grid_kr() const { return grid_R <= GB && grid_keeps_rows<V>(nb); }
+  // Whole solves in one launch up to GRID_MAX_P slices of grid_max_rows rows (524,288
+  // rows; complex 262,144), for everything but the literal order and ILU(0): there the
+  // multi-launch iteration waits for its launches more than for memory.  Time per
+  // iteration, multi-launch / whole solve: real n = 4 32.0 / 14.7 us at 46,656 rows, 35.1
+  // / 17.7 at 125,000, 42.5 / 26.3 at 250,047, 58.4 / 40.8 at 512,000; n = 16 90.4 / 66.5
+  // at 512,000; complex n = 16 102 / 62 at 250,047; BSR3 n = 8 57.4 / 40.8 at 255,552.
+  // Slices of GB rows, one row a thread, as long as GRID_MAX_P of them suffice: 1,024-row
+  // slices run 32,761 rows at 19.6 instead of 13.6 us, 256-row ones at 14.8.
+  void pick_grid() {
+    grid_P = 0;
+    if (literal || ilu) return;
+    const int P = std::min(GRID_MAX_P, (int)(((long long)N + GB - 1) / GB));
+    const int R = (int)(((long long)N + P - 1) / P + WAVE - 1) / WAVE * WAVE;
+    if (R > grid_max_rows<V>()) return;
+    grid_R = R;
+    grid_cap = grid_capacity<V>(nb, A.format == MLB_BSR3, grid_kr());
+    grid_P = (N + R - 1) / R;
+    if (grid_P > grid_cap) grid_P = 0;
+    // test hooks, read from the environment: a wait that gives up after so many tries (its solve
+    // fails with MLB_EHIP), and the time a group waits at its gate (0: it mostly leaves)
+    if (const char* e = std::getenv("MLB_GRID_MAX_TRIES")) {
+      const long v = std::strtol(e, nullptr, 10);
+      if (v > 0) grid_max_tries = (unsigned)std::min<long>(v, 0x7fffffffL);
+    }
+    if (const char* e = std::getenv("MLB_GRID_ENTRY_TICKS"))
+      grid_entry_ticks = std::max(0L, std::min(std::strtol(e, nullptr, 10), (long)GRID_ENTRY_TICKS));
+  }
+
+  // One system in one launch.  False: its group never was complete (nothing written).
+  bool grid_run(const V* b, V* x, double tol, long long maxit, double kappa, V* xrec, long long K,
+                long long stag_window, bool resid, GridOut& o) {
+    GridJob<V, Sc> J = grid_job(b, x, Q, ldq, tol, maxit, kappa, xrec, K, stag_window, resid);
+    GridOut* dout = reinterpret_cast<GridOut*>(part2);
+    J.out = dout;
+    auto* dj = reinterpret_cast<GridJob<V, Sc>*>(reinterpret_cast<char*>(part2) + 256);
+    static_assert(256 + sizeof(GridJob<V, Sc>) <= PSUM_GRID * (NMAX + 1) * sizeof(double), "job fits part2");
+    for (int t = 0; t < GRID_STARTS; ++t) {
+      GridGate gate(grid_P > 1 ? (double)grid_P / grid_cap : 0.0);
+      grid_launch<V>(dj, nullptr, &J, 1, grid_P, nb, A.format == MLB_BSR3, grid_kr(), &st->ctl[3], s);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(hipMemcpyAsync(&o, dout, sizeof(o), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      if (o.status == 1) return true;
+      if (o.status == 2) throw Error{MLB_EHIP, "a whole-solve launch gave up waiting for another workgroup"};
+    }
+    return false;
+  }
+  GridJob<V, Sc> grid_job(const V* b, V* x, const V* Q_, long long ldq_, double tol, long long maxit, double kappa,
+                          V* xrec, long long K, long long stag_window, bool resid) const {
+    GridJob<V, Sc> J;
+    J.N = N; J.n = n; J.P = grid_P; J.R = grid_R;
+    J.rp = A.rp; J.ci = A.ci; J.val = A.val;
+    J.rpT = AH.rp; J.ciT = AH.ci; J.valT = AH.val;
+    J.b = b; J.x = x; J.Q = Q_; J.ldq = ldq_;
+    J.G = G; J.W = W; J.F = F; J.r = r; J.xb = gt; J.xb1 = z;
+    J.slots = part; J.st = st;
+    J.xrec = xrec; J.K = K;
+    J.tol = tol; J.kappa = kappa; J.maxit = maxit; J.stag_window = stag_window;
+    J.tf = tf ? 1 : 0; J.resid = resid ? 1 : 0;
+    J.max_tries = grid_max_tries; J.entry_ticks = grid_entry_ticks;
+    return J;
   }
 
   void release() {
@@ -984,11 +1092,29 @@ struct Engine {
     long long iter;
     double err;
     float setup_ms;
+    double rr = -1.0, bb = 0.0;   // ||b - A x||^2 and ||b||^2 where the solve left them (rr >= 0)
   };
 
   // Algorithm 7.1 with M = I from x (in: x_0, out: solution).
   Out solve(const V* b, V* x, const V* Q_, long long ldq_, double tol, long long maxit, double kappa, V* xrec,
-            long long K, long long stag_window = 0) {
+            long long K, long long stag_window = 0, bool resid = false) {
+    if (grid_P) {
+      Q = Q_;
+      ldq = ldq_;
+      GridOut g{};
+      if (grid_run(b, x, tol, maxit, kappa, xrec, K, stag_window, resid, g)) {
+        Out o{};
+        o.flag = g.flag;
+        o.iter = g.iter;
+        o.err = g.err;
+        o.setup_ms = poll ? 0.f : (float)(g.setup_ticks * 1e-5);
+        if (resid) {
+          o.rr = g.rr;
+          o.bb = g.bb;
+        }
+        return o;
+      }
+    }
     if (poll) return solve_polled(b, x, Q_, ldq_, tol, maxit, kappa, xrec, K, stag_window);
     Q = Q_;
     ldq = ldq_;
@@ -1367,7 +1493,8 @@ static typename Engine<V64>::Out fp64_iteration(mlb_solver* h, Impl<V64, V32>& i
                                                 const V64* Q, long long ldq, long long maxit, V64* xrec, long long K) {
   const mlb_options& o = h->opt;
   precond_map(h, im, x, 1, h->N, false);
-  auto out = im.e64.solve(b, x, Q, ldq, o.tol, maxit, o.kappa, xrec, K);
+  // without a preconditioner the iteration's A is the caller's, and the launch may leave the true residual
+  auto out = im.e64.solve(b, x, Q, ldq, o.tol, maxit, o.kappa, xrec, K, 0, o.precond == MLB_PRECOND_NONE);
   precond_map(h, im, x, 1, h->N, true);
   if (xrec) precond_map(h, im, xrec, (int)std::min<long long>(K, std::max<long long>(out.iter, 0)), h->N, true);
   if (im.has_ilu) ilu_check(im.ilu, h->s);
@@ -1382,6 +1509,15 @@ static int solve_impl(mlb_solver* h, Impl<V64, V32>& im, const V64* b, V64* x, c
   SolveClock clock(h->s, h->noalloc);
   mlb_result R{};
   int flag = 1;
+  double left_rr = -1.0, left_bb = 0.0;   // sums of the true residual of the present x, when the solve left them
+  auto true_error = [&] {
+    double rr = left_rr, bb = left_bb;
+    if (rr < 0) {
+      im.e64.resid_sums(im.A0, b, x, im.r64);
+      im.e64.read_aux(&rr, &bb);
+    }
+    return std::sqrt(rr) / (bb > 0 ? std::sqrt(bb) : 1.0);
+  };
   if (o.precision == MLB_PREC_FP64) {
     auto out = fp64_iteration(h, im, b, x, Q, ldq, o.maxit, (V64*)o.iterates, o.record_iterates);
     flag = out.flag;
@@ -1389,16 +1525,16 @@ static int solve_impl(mlb_solver* h, Impl<V64, V32>& im, const V64* b, V64* x, c
     R.fp64_iters = out.iter;
     R.err_recursive = out.err;
     R.setup_ms = out.setup_ms;
+    left_rr = out.rr;
+    left_bb = out.bb;
     // restarts from the x reached while a converged run leaves the true residual above tol
     int restarts = 0;
     while (flag == 0 && restarts < o.max_restarts && R.iter < o.maxit) {
-      im.e64.resid_sums(im.A0, b, x, im.r64);
-      double rr, bb;
-      im.e64.read_aux(&rr, &bb);
-      const double et = std::sqrt(rr) / (bb > 0 ? std::sqrt(bb) : 1.0);
-      if (!(et >= o.tol)) break;
+      if (!(true_error() >= o.tol)) break;
       ++restarts;
       auto more = fp64_iteration(h, im, b, x, Q, ldq, o.maxit - R.iter, (V64*)nullptr, 0);
+      left_rr = more.rr;
+      left_bb = more.bb;
       flag = more.flag;
       R.iter += more.iter;
       R.fp64_iters += more.iter;
@@ -1461,6 +1597,8 @@ static int solve_impl(mlb_solver* h, Impl<V64, V32>& im, const V64* b, V64* x, c
     if (fallback) {
       long long left = std::max<long long>(1, o.maxit - used);
       auto out = fp64_iteration(h, im, b, x, Q, ldq, left, (V64*)nullptr, 0);
+      left_rr = out.rr;
+      left_bb = out.bb;
       flag = out.flag;
       R.fp64_iters = out.iter;
       R.iter = used + out.iter;
@@ -1468,10 +1606,7 @@ static int solve_impl(mlb_solver* h, Impl<V64, V32>& im, const V64* b, V64* x, c
     }
   }
   // true residual ||b - A x|| / ||b|| in fp64 with the caller's A
-  im.e64.resid_sums(im.A0, b, x, im.r64);
-  double rr, bb;
-  im.e64.read_aux(&rr, &bb);
-  R.err_true = std::sqrt(rr) / (bb > 0 ? std::sqrt(bb) : 1.0);
+  R.err_true = true_error();
   if (o.precision == MLB_PREC_FP32_IR && R.fp64_iters == 0) R.err_recursive = R.err_true;
   R.solve_ms = clock.stop_ms();
   R.flag = flag;
@@ -1652,7 +1787,7 @@ static int solve_solver(mlb_solver* h, const void* b, void* x, const void* Q, in
 
 // ------------------------------------------------------------------ batched small solves
 
-// Which prepared solvers the one-workgroup batch kernel takes.
+// Which prepared solvers a batched launch takes.
 static void check_batchable(const mlb_solver* h) {
   if (h->format != MLB_CSR) throw Error{MLB_EUNSUPPORTED, "batched solves take CSR matrices"};
   if (h->opt.precision != MLB_PREC_FP64) throw Error{MLB_EUNSUPPORTED, "batched solves run in fp64"};
@@ -1662,91 +1797,112 @@ static void check_batchable(const mlb_solver* h) {
   if (h->N > MLB_BATCH_MAX_N) throw Error{MLB_EUNSUPPORTED, "batched solves take at most MLB_BATCH_MAX_N rows"};
 }
 
-template <class V64, int NB>
-static void launch_small(const SmallJob<V64, typename traits<V64>::wide>* dj, int count, hipStream_t s) {
-  k_small<V64, typename traits<V64>::wide, NB><<<count, SB, 0, s>>>(dj);
+// Bytes of a batch's buffer: the job descriptors, their results, the map of at most
+// `wgs` logical workgroups and the claim counter.
+template <class V>
+static size_t batch_bytes(size_t count, size_t wgs) {
+  using Sc = typename traits<V>::wide;
+  return count * (sizeof(GridJob<V, Sc>) + sizeof(GridOut)) + wgs * sizeof(int2) + 16;
 }
 
-// Runs the systems of hs (same dtype, same stream) in one launch of k_small and
+// Runs the systems of hs (same dtype, same stream) in one launch of k_grid and
 // fills res[k] as mlbicgstab_solve would.
-// job_buf: a device buffer for at least `count` job descriptors, or NULL to
-// allocate one for the call (the serving batchers keep one each).
+// job_buf: a device buffer of job_cap bytes, or NULL to allocate one for the call
+// (the serving batchers keep one each).
 template <class V64, class V32>
 static void batch_impl(mlb_solver* const* hs, int count, const void* const* b, void* const* x,
                        const void* const* Q, const int64_t* ldq, mlb_result* res,
-                       Impl<V64, V32>* (*impl_of)(mlb_solver*), void* job_buf) {
+                       Impl<V64, V32>* (*impl_of)(mlb_solver*), void* job_buf, size_t job_cap) {
   using Sc = typename traits<V64>::wide;
+  using Job = GridJob<V64, Sc>;
   hipStream_t s = hs[0]->s;
-  std::vector<SmallJob<V64, Sc>> jobs((size_t)count);
   int nb = 4;
+  std::vector<int> todo;
+  for (int k = 0; k < count; ++k) nb = std::max(nb, bucket(impl_of(hs[k])->e64.n));
+  bool kr = grid_keeps_rows<V64>(nb);
+  for (int k = 0; k < count; ++k) kr = kr && impl_of(hs[k])->e64.grid_R <= GB;
+  const int cap = grid_capacity<V64>(nb, 0, kr);
   for (int k = 0; k < count; ++k) {
-    Engine<V64>& e = impl_of(hs[k])->e64;
-    SmallJob<V64, Sc>& J = jobs[(size_t)k];
-    J.N = e.N;
-    J.n = e.n;
-    J.rp = e.A.rp;
-    J.ci = e.A.ci;
-    J.val = e.A.val;
-    J.rpT = e.AH.rp;
-    J.ciT = e.AH.ci;
-    J.valT = e.AH.val;
-    J.b = (const V64*)b[k];
-    J.x = (V64*)x[k];
-    J.Q = (const V64*)Q[k];
-    J.ldq = ldq[k];
-    J.G = e.G;
-    J.W = e.W;
-    J.F = e.F;
-    J.r = e.r;
-    J.gt = e.gt;
-    J.z = e.z;
-    J.st = e.st;
-    J.tol = hs[k]->opt.tol;
-    J.kappa = hs[k]->opt.kappa;
-    J.maxit = hs[k]->opt.maxit;
-    J.host_done = e.host_done_dev;
-    J.tf = e.tf ? 1 : 0;
-    J.xrec = (V64*)hs[k]->opt.iterates;
-    J.K = hs[k]->opt.record_iterates > 0 ? std::min<long long>(hs[k]->opt.record_iterates, hs[k]->opt.maxit) : 0;
-    *(volatile int*)e.host_done = 0;
-    nb = std::max(nb, bucket(e.n));
+    const int P = impl_of(hs[k])->e64.grid_P;
+    if (P && P <= cap) todo.push_back(k);
+    else solve_solver(hs[k], b[k], x[k], Q[k], ldq[k], res ? res + k : nullptr);   // too large for a group
   }
   Allocs tmp(s, false);
-  auto* dj = job_buf ? (SmallJob<V64, Sc>*)job_buf : tmp.get<SmallJob<V64, Sc>>((size_t)count);
-  HIP_TRY(hipMemcpyAsync(dj, jobs.data(), sizeof(SmallJob<V64, Sc>) * count, hipMemcpyHostToDevice, s));
-  hipEvent_t t0, t1;
-  HIP_TRY(hipEventCreate(&t0));
-  HIP_TRY(hipEventCreate(&t1));
-  HIP_TRY(hipEventRecord(t0, s));
-  switch (nb) {
-    case 4: launch_small<V64, 4>(dj, count, s); break;
-    case 8: launch_small<V64, 8>(dj, count, s); break;
-    case 16: launch_small<V64, 16>(dj, count, s); break;
-    default: launch_small<V64, 32>(dj, count, s); break;
-  }
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipEventRecord(t1, s));
-  HIP_TRY(hipEventSynchronize(t1));
-  float ms = 0;
-  HIP_TRY(hipEventElapsedTime(&ms, t0, t1));
-  (void)hipEventDestroy(t0);
-  (void)hipEventDestroy(t1);
-  for (int k = 0; k < count; ++k) {
-    Impl<V64, V32>& im = *impl_of(hs[k]);
-    State<Sc> st;
-    HIP_TRY(hipMemcpyAsync(&st, im.e64.st, sizeof(State<Sc>), hipMemcpyDeviceToHost, s));
-    im.e64.resid_sums(im.A0, (const V64*)b[k], (const V64*)x[k], im.r64);
-    double rr, bb;
-    im.e64.read_aux(&rr, &bb);   // synchronises the stream (st is then valid too)
-    mlb_result R{};
-    R.flag = st.done ? st.flag : 1;
-    R.iter = st.iter;
-    R.fp64_iters = st.iter;
-    R.err_recursive = st.err;
-    R.err_true = std::sqrt(rr) / (bb > 0 ? std::sqrt(bb) : 1.0);
-    R.solve_ms = ms;
-    if (res) res[k] = R;
-    hs[k]->solved = true;
+  struct Events {
+    hipEvent_t t0 = nullptr, t1 = nullptr;
+    ~Events() {
+      if (t0) (void)hipEventDestroy(t0);
+      if (t1) (void)hipEventDestroy(t1);
+    }
+  } ev;
+  HIP_TRY(hipEventCreate(&ev.t0));
+  HIP_TRY(hipEventCreate(&ev.t1));
+  // a system whose group left at its gate is started again
+  for (int start = 0; !todo.empty(); ++start) {
+    if (start == GRID_STARTS) throw Error{MLB_EHIP, "a batched system's workgroups were never all running"};
+    const size_t m = todo.size();
+    size_t wgs = 0;
+    int waiting = 0;   // workgroups that wait for others
+    for (int k : todo) {
+      const int P = impl_of(hs[k])->e64.grid_P;
+      wgs += P;
+      if (P > 1) waiting += P;
+    }
+    const size_t bytes = batch_bytes<V64>(m, wgs);
+    char* buf = job_buf && bytes <= job_cap ? (char*)job_buf : tmp.get<char>(bytes);
+    Job* dj = (Job*)buf;
+    GridOut* dout = (GridOut*)(dj + m);
+    int2* dmap = (int2*)(dout + m);
+    unsigned* tick = (unsigned*)(dmap + wgs);
+    std::vector<char> host(bytes);
+    Job* hj = (Job*)host.data();
+    int2* hm = (int2*)(host.data() + ((char*)dmap - buf));
+    for (size_t q = 0; q < m; ++q) {
+      const int k = todo[q];
+      const mlb_options& o = hs[k]->opt;
+      const Engine<V64>& e = impl_of(hs[k])->e64;
+      Job J = e.grid_job((const V64*)b[k], (V64*)x[k], (const V64*)Q[k], ldq[k], o.tol, o.maxit, o.kappa,
+                         (V64*)o.iterates, o.record_iterates > 0 ? o.record_iterates : 0, 0, true);
+      J.out = dout + q;
+      memcpy((void*)(hj + q), &J, sizeof(Job));
+      for (int p = 0; p < e.grid_P; ++p) *hm++ = make_int2((int)q, p);
+    }
+    HIP_TRY(hipMemcpyAsync(buf, host.data(), bytes, hipMemcpyHostToDevice, s));
+    std::vector<GridOut> out(m);
+    {
+      GridGate gate((double)waiting / cap);
+      HIP_TRY(hipEventRecord(ev.t0, s));
+      grid_launch<V64>(dj, dmap, nullptr, (int)m, (int)wgs, nb, 0, kr, tick, s);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(hipEventRecord(ev.t1, s));
+      HIP_TRY(hipMemcpyAsync(out.data(), dout, sizeof(GridOut) * m, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+    }
+    float ms = 0;
+    HIP_TRY(hipEventElapsedTime(&ms, ev.t0, ev.t1));
+    std::vector<int> again;
+    for (size_t q = 0; q < m; ++q) {
+      const int k = todo[q];
+      const GridOut& o = out[q];
+      if (o.status == 2) throw Error{MLB_EHIP, "a batched solve gave up waiting for another workgroup"};
+      if (o.status == 0) {
+        again.push_back(k);
+        continue;
+      }
+      mlb_result R{};
+      R.flag = o.flag;
+      R.iter = o.iter;
+      R.fp64_iters = o.iter;
+      R.err_recursive = o.err;
+      R.err_true = std::sqrt(o.rr) / (o.bb > 0 ? std::sqrt(o.bb) : 1.0);
+      R.solve_ms = ms;
+      if (res) res[k] = R;
+      Engine<V64>& e = impl_of(hs[k])->e64;
+      e.Q = (const V64*)Q[k];
+      e.ldq = ldq[k];
+      hs[k]->solved = true;
+    }
+    todo.swap(again);
   }
 }
 
@@ -1754,7 +1910,8 @@ static Impl<double, float>* real_impl(mlb_solver* h) { return h->real.get(); }
 static Impl<cplx<double>, cplx<float>>* cplx_impl(mlb_solver* h) { return h->cpx.get(); }
 
 static int solve_batch(mlb_solver* const* hs, int count, const void* const* b, void* const* x, const void* const* Q,
-                       const int64_t* ldq, mlb_result* res, void* job_buf = nullptr) {
+                       const int64_t* ldq, mlb_result* res, void* job_buf = nullptr,
+                       size_t job_cap = 0) {
   if (!hs || !b || !x || !Q || !ldq) throw Error{MLB_EINVAL, "handles, b, x, Q and ldq must be non-NULL"};
   if (count < 1 || count > MLB_BATCH_MAX) throw Error{MLB_EINVAL, "count must be in [1, MLB_BATCH_MAX]"};
   for (int k = 0; k < count; ++k) {
@@ -1766,9 +1923,9 @@ static int solve_batch(mlb_solver* const* hs, int count, const void* const* b, v
     check_batchable(hs[k]);
   }
   if (hs[0]->real)
-    batch_impl(hs, count, b, x, Q, ldq, res, real_impl, job_buf);
+    batch_impl(hs, count, b, x, Q, ldq, res, real_impl, job_buf, job_cap);
   else
-    batch_impl(hs, count, b, x, Q, ldq, res, cplx_impl, job_buf);
+    batch_impl(hs, count, b, x, Q, ldq, res, cplx_impl, job_buf, job_cap);
   return 0;
 }
 
@@ -2291,8 +2448,8 @@ static void batcher_main(Server* S) {
   hipStream_t st = nullptr;
   int* flags = nullptr;
   void* jobs = nullptr;   // job descriptors of one batch, kept for the batcher's life
-  const size_t job_bytes = BATCH_CAP * std::max(sizeof(SmallJob<double, double>),
-                                                sizeof(SmallJob<cplx<double>, cplx<double>>));
+  const size_t job_bytes = std::max(batch_bytes<double>(BATCH_CAP, BATCH_CAP * 16),
+                                    batch_bytes<cplx<double>>(BATCH_CAP, BATCH_CAP * 16));
   bool ok = hipSetDevice(S->device) == hipSuccess && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
             hipHostMalloc((void**)&flags, 2 * BATCH_CAP * sizeof(int), hipHostMallocMapped) == hipSuccess &&
             hipMalloc(&jobs, job_bytes) == hipSuccess;
@@ -2370,7 +2527,8 @@ static void batcher_main(Server* S) {
         if (part.empty()) continue;
         std::vector<mlb_result> res(part.size());
         try {
-          solve_batch(part.data(), (int)part.size(), pb.data(), px.data(), pq.data(), pl.data(), res.data(), jobs);
+          solve_batch(part.data(), (int)part.size(), pb.data(), px.data(), pq.data(), pl.data(), res.data(), jobs,
+                      job_bytes);
           for (size_t q = 0; q < part.size(); ++q) {
             batch[pi[q]]->res = res[q];
             batch[pi[q]]->rc = res[q].flag;

@@ -116,6 +116,7 @@ struct State {
   Sc alph[NMAX];
   int npend;
   int npad_;
+  unsigned ctl[4];      // words of a whole-solve launch (mlb_grid.hpp): arrivals, gate, lost wait, claim counter
   Sc S[NMAX * NMAX];    // S[s * NMAX + u] = q_s^H w_u  (s >= u); last, so rows s >= n can be left out of copies
 };
 
