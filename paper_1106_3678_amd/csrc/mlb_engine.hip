@@ -258,29 +258,72 @@ struct IluFactor {
   V* dinv = nullptr;                  // inverse diagonal (blocks) of F (U_ii^{-1}) and FH ((U_ii^H)^{-1})
   V* dinvH = nullptr;
   int* ordL = nullptr;                                                         // rows by level of L (device)
-  int4 *lvL = nullptr, *lvU = nullptr, *lvHf = nullptr, *lvHb = nullptr;       // the solves' rows and ranges
+  IluRows<V> rowsL, rowsU, rowsHf, rowsHb;                                      // the solves' rows in solve order
   std::vector<int> ptrL;                                                       // level pointers of L (host)
-  V* tmid = nullptr;                  // intermediate vector of the two solves
+  V* tmid = nullptr;                  // the first solve's output in its order, which the second reads
+  V* tend = nullptr;                  // the second's, in its own
   unsigned* ctl = nullptr;            // one-launch solves: claim counters [0] and [1], lost-wait flag [2]
-  int sweep_grid = 1;                 // their workgroups (persistent: each wave claims until none are left)
+  int block = 1;                      // (block) rows of a workgroup
+  IluLds lds;                         // and how it uses its LDS
   unsigned max_tries = ~0u;           // tries of a row before it gives up (MLB_ILU_MAX_TRIES, for tests)
 };
 
-// Waves of a one-launch triangular solve, as a multiple of the waves one
-// average level fills (capped at two per CU), one wave per workgroup so that
-// they spread over the CUs.
-static constexpr double ILU_SWEEP_LEVEL_MULT = 3.0;
+// (Block) rows of a workgroup of a one-launch solve.  A solve takes about the time of one
+// block, some 300 rows a us, plus 2.6 us of hand-over from each block to the next, so the
+// best block grows with the root of m.  96^3 (884,736 rows), n = 4, ms a solve with blocks
+// of 9,216 / 16,384 / 18,816 / 24,576 rows: 37.6 / 32.0 / 31.5 / 31.6; 42,408 rows of 3x3
+// blocks with 1,767 / 3,534 / 4,118 / 5,301: 14.3 / 13.1 / 13.4 / 13.1.
+static int ilu_block_rows(int m) {
+  const int best = (int)std::sqrt(400.0 * m);
+  return std::max(WAVE, (best + WAVE - 1) / WAVE * WAVE);
+}
+
+// The ring and the slots of a workgroup for entries of bs x bs values of `words` 64-bit
+// words, w packed a row, in the LDS of the device: 16 slots for 12 loader waves (8 for 6 of
+// 3x3 blocks) where they fit, and a ring that covers two levels of a wide block.
+static IluLds ilu_lds(int bs, int words, int w) {
+  int dev = 0, lds = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || lds <= 0) {
+    (void)hipGetLastError();
+    lds = 64 << 10;
+  }
+  const size_t slot = (size_t)ilu_slot_words(bs, words, w) * 8, place = (size_t)bs * words * 8;
+  const size_t room = (size_t)lds - 1024;
+  IluLds r;
+  r.ring = bs == 1 ? 8192 : 1024;
+  while (r.ring > 512 && r.ring * place > room / 2) r.ring /= 2;
+  r.slots = (int)std::min<size_t>(bs == 1 ? 16 : 8, (room - r.ring * place) / slot);
+  while (r.slots > 2 && r.ring - 128 * r.slots < r.ring / 3) --r.slots;
+  if (r.slots < 1) throw Error{MLB_EUNSUPPORTED, "ILU(0): the device's LDS is too small for a triangular solve"};
+  r.safe = std::max(0, r.ring - 128 * r.slots);
+  r.bytes = r.ring * place + r.slots * slot;
+  return r;
+}
+
+static int ilu_width(long long nnz, int m);
 
 static int level_grid(int count) { return std::max(1, std::min((count + BLOCK - 1) / BLOCK, 4096)); }
 
-// The rows of a sweep in solve order with their entry ranges (host): {i, q0, q1, 0},
+// The rows of a solve in solve order with their entry ranges (host): {i, q0, q1, 0},
 // [q0, q1) the stored entries left (lower) or right of row i's diagonal.  Every row
-// has a stored diagonal (checked before).
+// has a stored diagonal (checked before).  ord: the rows by level; the solve order is by
+// block, first from the first row (lower) or the last, and by level inside a block.
+// cstart, bchunk: the chunks (see IluRows); ptr: the level pointers of ord.
 static std::vector<int4> level_rows(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<int>& ord,
-                                    bool lower) {
-  std::vector<int4> out(ord.size());
-  for (size_t t = 0; t < ord.size(); ++t) {
-    const int i = ord[t];
+                                    const std::vector<int>& ptr, bool lower, int block, std::vector<int>& cstart,
+                                    std::vector<int>& bchunk) {
+  const size_t m = ord.size();
+  std::vector<int> lev(m);   // level of every position
+  size_t level = 0;
+  std::vector<int4> out(m);
+  std::vector<int> fill((m + block - 1) / block);
+  for (size_t k = 0; k < fill.size(); ++k) fill[k] = (int)(k * block);
+  for (size_t r = 0; r < m; ++r) {
+    const int i = ord[r];
+    while ((int)r >= ptr[level + 1]) ++level;
+    const int t = fill[(lower ? (size_t)i : m - 1 - i) / block]++;
+    lev[t] = (int)level;
     int qd = rp[i];
     for (int q = rp[i]; q < rp[i + 1]; ++q)
       if (ci[q] == i) {
@@ -289,16 +332,34 @@ static std::vector<int4> level_rows(const std::vector<int>& rp, const std::vecto
       }
     out[t] = make_int4(i, lower ? rp[i] : qd + 1, lower ? qd : rp[i + 1], 0);
   }
+  // chunks: at most 64 positions of one level of one block
+  cstart.clear();
+  bchunk.assign(1, 0);
+  for (size_t t = 0; t < m; ++t)
+    if (t % block == 0 || lev[t] != lev[t - 1] || (int)t - cstart.back() == WAVE) {
+      if (t && t % block == 0) bchunk.push_back((int)cstart.size());
+      cstart.push_back((int)t);
+    }
+  bchunk.push_back((int)cstart.size());
+  cstart.push_back((int)m);
   return out;
 }
 
-// One triangular solve in one launch (k_ilu_solve_sweep); `which` picks its claim counter.
+// One triangular solve in one launch (k_ilu_solve_block); `which` picks its claim counter.
 template <class V, int BS, bool LOWER, bool UNIT>
-static void ilu_sweep1(const IluFactor<V>& f, const Mat<V>& M, const V* dinv, const int4* lv, const V* in, V* out,
+static void ilu_solve1(const IluFactor<V>& f, const Mat<V>& M, const IluRows<V>& rows, const V* in, V* xch, V* out,
                        V* next, int which, hipStream_t s, const int* done) {
-  k_ilu_solve_sweep<V, BS, LOWER, UNIT><<<f.sweep_grid, WAVE, 0, s>>>(M.ci, M.val, dinv, lv, f.nbrows, in, out,
-                                                                       next, f.ctl + which, f.ctl + 2, f.max_tries,
-                                                                       done);
+  k_ilu_solve_block<V, BS, LOWER, UNIT><<<(f.nbrows + f.block - 1) / f.block, ilu_threads<BS>(), f.lds.bytes, s>>>(
+      M.ci, M.val, rows, f.nbrows, f.block, f.lds, in, xch, out, next, f.ctl + which, f.ctl + 2, f.max_tries, done);
+}
+
+// Lets the four kernels of one factor take the LDS a block needs.
+template <class V, int BS>
+static void ilu_allow_lds(int lds) {
+  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
 }
 
 // Marks f.tmid pending and resets both claim counters: the start of a pair of one-launch solves.
@@ -316,11 +377,11 @@ static void ilu_apply(const IluFactor<V>& f, const V* in, V* out, hipStream_t s,
   } else {
     ilu_pending(f, s, done);
     if (f.bs == 1) {
-      ilu_sweep1<V, 1, true, true>(f, f.F, f.dinv, f.lvL, in, f.tmid, out, 0, s, done);
-      ilu_sweep1<V, 1, false, false>(f, f.F, f.dinv, f.lvU, f.tmid, out, nullptr, 1, s, done);
+      ilu_solve1<V, 1, true, true>(f, f.F, f.rowsL, in, f.tmid, nullptr, f.tend, 0, s, done);
+      ilu_solve1<V, 1, false, false>(f, f.F, f.rowsU, f.tmid, f.tend, out, nullptr, 1, s, done);
     } else {
-      ilu_sweep1<V, 3, true, true>(f, f.F, f.dinv, f.lvL, in, f.tmid, out, 0, s, done);
-      ilu_sweep1<V, 3, false, false>(f, f.F, f.dinv, f.lvU, f.tmid, out, nullptr, 1, s, done);
+      ilu_solve1<V, 3, true, true>(f, f.F, f.rowsL, in, f.tmid, nullptr, f.tend, 0, s, done);
+      ilu_solve1<V, 3, false, false>(f, f.F, f.rowsU, f.tmid, f.tend, out, nullptr, 1, s, done);
     }
   }
 }
@@ -333,11 +394,11 @@ static void ilu_apply_h(const IluFactor<V>& f, V* v, hipStream_t s, const int* d
   } else {
     ilu_pending(f, s, done);
     if (f.bs == 1) {
-      ilu_sweep1<V, 1, true, false>(f, f.FH, f.dinvH, f.lvHf, v, f.tmid, v, 0, s, done);
-      ilu_sweep1<V, 1, false, true>(f, f.FH, f.dinvH, f.lvHb, f.tmid, v, nullptr, 1, s, done);
+      ilu_solve1<V, 1, true, false>(f, f.FH, f.rowsHf, v, f.tmid, nullptr, f.tend, 0, s, done);
+      ilu_solve1<V, 1, false, true>(f, f.FH, f.rowsHb, f.tmid, f.tend, v, nullptr, 1, s, done);
     } else {
-      ilu_sweep1<V, 3, true, false>(f, f.FH, f.dinvH, f.lvHf, v, f.tmid, v, 0, s, done);
-      ilu_sweep1<V, 3, false, true>(f, f.FH, f.dinvH, f.lvHb, f.tmid, v, nullptr, 1, s, done);
+      ilu_solve1<V, 3, true, false>(f, f.FH, f.rowsHf, v, f.tmid, nullptr, f.tend, 0, s, done);
+      ilu_solve1<V, 3, false, true>(f, f.FH, f.rowsHb, f.tmid, f.tend, v, nullptr, 1, s, done);
     }
   }
 }
@@ -387,6 +448,7 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   f.dpos = al.get<int>(m);
   f.dinv = al.get<V>((size_t)m * b2);
   f.tmid = al.get<V>((size_t)m * bs);
+  f.tend = al.get<V>((size_t)m * bs);
   f.ctl = al.get<unsigned>(4);
   k_fill<unsigned><<<1, BLOCK, 0, s>>>(f.ctl, 4, 0u);
   // a test hook: a positive MLB_ILU_MAX_TRIES makes every row that waits that many tries give up
@@ -414,15 +476,37 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   HIP_TRY(hipMemcpyAsync(f.ordL, ord.data(), sizeof(int) * m, hipMemcpyHostToDevice, s));
   std::vector<int> ordU, ptrU;
   level_sets(hrp, hci, false, ordU, ptrU);
-  {
-    const double level_waves = (double)m / (double)std::max<size_t>(1, f.ptrL.size() - 1) / WAVE;
-    f.sweep_grid = (int)std::min<double>(2.0 * device_cus(), std::max(1.0, ILU_SWEEP_LEVEL_MULT * level_waves));
-  }
-  const std::vector<int4> lvL = level_rows(hrp, hci, ord, true), lvU = level_rows(hrp, hci, ordU, false);
-  f.lvL = al.get<int4>(m);
-  f.lvU = al.get<int4>(m);
-  HIP_TRY(hipMemcpyAsync(f.lvL, lvL.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(f.lvU, lvU.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
+  const int w = ilu_width(A.nnz, m);
+  f.block = ilu_block_rows(m);
+  f.lds = ilu_lds(bs, (int)sizeof(V) / 8, w);
+  if (bs == 1) ilu_allow_lds<V, 1>((int)f.lds.bytes);
+  else ilu_allow_lds<V, 3>((int)f.lds.bytes);
+  // the rows of a solve with factor matrix M (index arrays mrp, mci on the host)
+  auto rows = [&](IluRows<V>& r, const std::vector<int>& mrp, const std::vector<int>& mci, const std::vector<int>& o,
+                  const std::vector<int>& ptr, bool lower, bool diag) {
+    std::vector<int> cstart, bchunk;
+    const std::vector<int4> lv = level_rows(mrp, mci, o, ptr, lower, f.block, cstart, bchunk);
+    r.w = w;
+    r.lv = al.get<int4>(m);
+    r.src = al.get<int>(m);
+    r.pos = al.get<int>(m);
+    r.pc = al.get<int>((size_t)m * w);
+    r.pv = al.get<V>((size_t)m * w * b2);
+    if (diag) r.pd = al.get<V>((size_t)m * b2);
+    r.cstart = al.get<int>(cstart.size());
+    r.bchunk = al.get<int>(bchunk.size());
+    HIP_TRY(hipMemcpyAsync(r.lv, lv.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(r.cstart, cstart.data(), sizeof(int) * cstart.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(r.bchunk, bchunk.data(), sizeof(int) * bchunk.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));   // the host vectors are copied before they go
+  };
+  auto pack = [&](const Mat<V>& M, const V* dinv, const IluRows<V>& r, const IluRows<V>* before) {
+    k_ilu_positions<<<grid_for(m, 4096), BLOCK, 0, s>>>(r.lv, m, r.pos, before ? before->pos : nullptr, r.src);
+    if (bs == 1) k_ilu_pack<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(M.ci, M.val, dinv, r, m, f.block, f.lds.safe, !before);
+    else k_ilu_pack<V, 3><<<grid_for(m, 4096), BLOCK, 0, s>>>(M.ci, M.val, dinv, r, m, f.block, f.lds.safe, !before);
+  };
+  rows(f.rowsL, hrp, hci, ord, f.ptrL, true, false);
+  rows(f.rowsU, hrp, hci, ordU, ptrU, false, true);
   // factorisation, one launch per level of L
   for (size_t l = 0; l + 1 < f.ptrL.size(); ++l) {
     const int c = f.ptrL[l + 1] - f.ptrL[l];
@@ -448,19 +532,28 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   std::vector<int> ordHf, ordHb, ptrHf, ptrHb;
   level_sets(hrpH, hciH, true, ordHf, ptrHf);
   level_sets(hrpH, hciH, false, ordHb, ptrHb);
-  const std::vector<int4> lvHf = level_rows(hrpH, hciH, ordHf, true), lvHb = level_rows(hrpH, hciH, ordHb, false);
-  f.lvHf = al.get<int4>(m);
-  f.lvHb = al.get<int4>(m);
-  HIP_TRY(hipMemcpyAsync(f.lvHf, lvHf.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(f.lvHb, lvHb.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
+  rows(f.rowsHf, hrpH, hciH, ordHf, ptrHf, true, true);
+  rows(f.rowsHb, hrpH, hciH, ordHb, ptrHb, false, false);
+  pack(f.F, f.dinv, f.rowsL, nullptr);   // lower solves first
+  pack(f.F, f.dinv, f.rowsU, &f.rowsL);
+  pack(f.FH, f.dinvH, f.rowsHf, nullptr);
+  pack(f.FH, f.dinvH, f.rowsHb, &f.rowsHf);
+  HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));   // the host vectors above are copied before they go
+}
+
+// Packed entries of a row: the mean number of entries on one side of the diagonal,
+// rounded up, at most ILU_W.
+static int ilu_width(long long nnz, int m) {
+  return (int)std::max<long long>(1, std::min<long long>(ILU_W, (nnz - m + 2LL * m - 1) / (2LL * m)));
 }
 
 // Device bytes build_ilu allocates (beside the transpose's own temporaries).
 static size_t ilu_bytes(long long nnz, int m, int bs, size_t sv) {
   const size_t b2 = (size_t)bs * bs;
   return (size_t)nnz * 4 * 2 + (size_t)nnz * b2 * sv * 2 + (size_t)(m + 1) * 4 + (size_t)m * 4 * 3 +
-         (size_t)m * sizeof(int4) * 4 + (size_t)m * b2 * sv * 2 + (size_t)m * bs * sv + 16;
+         (size_t)m * (sizeof(int4) + 12 + ilu_width(nnz, m) * (4 + b2 * sv)) * 4 + (size_t)m * b2 * sv * 4 +
+         (size_t)m * bs * sv * 2 + 16;
 }
 
 // ------------------------------------------------------------------ launch dispatch
