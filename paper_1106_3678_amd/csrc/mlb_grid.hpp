@@ -22,8 +22,8 @@
 // cache is written back or invalidated, and one store and one load are all the
 // latency of a reduction or an exchange.
 // Words are marked pending again once everybody has read them:
-//  * slots: phase q uses ring position q mod 4.  A workgroup that has read all
-//    sums of phase q + 1 knows that everybody has finished reading phase q (they
+//  * slots: phase q uses ring position q mod 4.  A workgroup all of whose waves
+//    have read their sums of phase q + 1 knows that everybody has finished reading phase q (they
 //    published q + 1 afterwards) and marks its words of phase q; it waits for
 //    its outstanding stores before it publishes phase q + 2, so a reader that
 //    has passed q + 3 finds them pending, or the new ones of q + 4.
@@ -509,12 +509,13 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
       }
       if (kl >= 6) tot[tid] = t;
       else if (lane >= WAVE - KS) tot[wid * KS + k] = t;
-      // everybody has read the previous reduction's words
+      __syncthreads();
+      // This workgroup has seen the words of all P (each wave those of some of them, so only
+      // after the barrier): everybody has read the previous reduction's.
       U64* prev = reinterpret_cast<U64*>(J.slots) + (size_t)((q_ring + GRID_RING - 1) % GRID_RING) * COPIES * NS * P;
-      for (int w = tid; w < COPIES * NA * WS; w += GB)
+      for (int w = tid - 2 * WAVE; w >= 0 && w < COPIES * NA * WS; w += GB - 2 * WAVE)   // not the waves at work below
         grid_st(prev + ((size_t)(w / (NA * WS)) * P + rank) * NS + w % (NA * WS), (U64)pending64);
       q_ring = (q_ring + 1) % GRID_RING;
-      __syncthreads();
       if (wid < 2) {
         const int rows = kl >= 7 ? GB >> kl : NW;
         for (int w = lane; w < nw; w += WAVE) {

@@ -132,7 +132,7 @@ def test_threads_and_streams():
         with torch.cuda.stream(st):
             x = torch.zeros(p.N, dtype=torch.float64, device="cuda")
             s = binding.Solver(dA, p.n, tol=p.tol, maxit=p.maxit, stream=st)
-            for _ in range(3):
+            for _ in range(10):
                 x.zero_()
                 r = s.solve(b, x, Q)
             st.synchronize()
