@@ -810,12 +810,14 @@ struct Engine {
   }
 
   bool grid_kr() const { return grid_R <= GB && grid_keeps_rows<V>(nb); }
-  // Whole solves in one launch up to GRID_MAX_P slices of grid_max_rows rows (524,288
-  // rows; complex 262,144), for everything but the literal order and ILU(0): there the
-  // multi-launch iteration waits for its launches more than for memory.  Time per
-  // iteration, multi-launch / whole solve: real n = 4 32.0 / 14.7 us at 46,656 rows, 35.1
-  // / 17.7 at 125,000, 42.5 / 26.3 at 250,047, 58.4 / 40.8 at 512,000; n = 16 90.4 / 66.5
-  // at 512,000; complex n = 16 102 / 62 at 250,047; BSR3 n = 8 57.4 / 40.8 at 255,552.
+  // Whole solves in one launch up to GRID_MAX_P slices of grid_max_rows rows (1,048,576
+  // rows; complex 524,288; half of that for 3x3 blocks), for everything but the literal
+  // order and ILU(0): there the multi-launch iteration waits for its launches more than
+  // for memory.  Time per iteration, multi-launch / whole solve: real n = 4 32.0 / 14.7 us
+  // at 46,656 rows, 35.1 / 17.7 at 125,000, 42.5 / 26.3 at 250,047, 58.4 / 40.8 at 512,000,
+  // 80.0 / 68.8 at 1,000,000; n = 8 96.2 / 88.7 at 1,000,000; complex n = 16 102 / 62 at
+  // 250,047, 152 / 124 at 512,000; fp32 n = 4 60.3 / 55.7 at 1,000,000; 3x3 blocks n = 8
+  // 57.4 / 40.8 at 255,552, 72.2 / 65.8 at 499,125, but 89.5 / 97.7 at 714,984.
   // Slices of GB rows, one row a thread, as long as GRID_MAX_P of them suffice: 1,024-row
   // slices run 32,761 rows at 19.6 instead of 13.6 us, 256-row ones at 14.8.
   void pick_grid() {
@@ -823,7 +825,7 @@ struct Engine {
     if (literal || ilu) return;
     const int P = std::min(GRID_MAX_P, (int)(((long long)N + GB - 1) / GB));
     const int R = (int)(((long long)N + P - 1) / P + WAVE - 1) / WAVE * WAVE;
-    if (R > grid_max_rows<V>()) return;
+    if (R > grid_max_rows<V>() / (A.format == MLB_BSR3 ? 2 : 1)) return;
     grid_R = R;
     grid_cap = grid_capacity<V>(nb, A.format == MLB_BSR3, grid_kr());
     grid_P = (N + R - 1) / R;

@@ -49,9 +49,9 @@ constexpr int GRID_MAX_P = 256;         // workgroups of one system, at most
 // Wall-clock ticks (s_memrealtime, 100 MHz)
 constexpr long long GRID_ENTRY_TICKS = 20000000;    // 0.2 s for the group to be complete
 constexpr long long GRID_WAIT_TICKS = 200000000;    // 2 s for any word, far beyond a legitimate wait
-// Rows of a workgroup's slice, at most: two LDS copies of a slice
+// Rows of a workgroup's slice, at most: two LDS copies of a slice (64 KB of the CU's 160)
 template <class V>
-constexpr int grid_max_rows() { return sizeof(V) > 8 ? 1024 : 2048; }
+constexpr int grid_max_rows() { return sizeof(V) > 8 ? 2048 : 4096; }
 
 // words of the state's ctl
 enum { GRID_ARRIVED = 0, GRID_GATE = 1, GRID_ERR = 2 };
@@ -1085,7 +1085,8 @@ __global__ __launch_bounds__(GB) void k_grid(const GridJob<V, Sc>* __restrict__ 
   static_assert(sizeof(State<Sc>) % 8 == 0, "state is copied in 8-byte words");
   __shared__ State<Sc> ss;
   __shared__ double sums[2 * (NB + 1) * (sizeof(Sc) / 8)];   // a copy each for waves 0 and 1
-  __shared__ V gl[grid_max_rows<V>()], zl[grid_max_rows<V>()];
+  constexpr int ROWS = KR ? GB : grid_max_rows<V>();
+  __shared__ V gl[ROWS], zl[ROWS];
   __shared__ int lost, ticket, gate;
   __shared__ long long setup_end;
   const long long start = wall_clock64();

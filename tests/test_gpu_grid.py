@@ -1,6 +1,6 @@
 """Whole solves in one launch, a group of workgroups per system: sizes at the edges of its slices.
 
-A system of up to 524,288 rows (complex 262,144) is solved by P = ceil(N / 512) workgroups, at most
+A system of up to 1,048,576 rows (complex and 3x3 blocks 524,288) is solved by P = ceil(N / 512) workgroups, at most
 256, each with its own rows (one row a thread in registers up to 512 rows a workgroup, else from
 memory).  The sizes below sit at the edges of a wave, of a slice, of the group and of both variants;
 the random patterns make every workgroup read rows of every other, with rows of up to 21 entries
@@ -95,9 +95,9 @@ def upload(p):
     return dA, torch.from_numpy(p.b).cuda(), binding.column_major(p.Q)
 
 
-@pytest.mark.parametrize("m,n", [(362, 2), (363, 4), (512, 1), (724, 4)])
+@pytest.mark.parametrize("m,n", [(362, 2), (363, 4), (512, 1), (724, 4), (1024, 2)])
 def test_slices_up_to_the_limit(m, n):
-    """131,044, 131,769 (the first past 256 x 512 rows), 262,144 and 524,176 rows."""
+    """131,044, 131,769 (the first past 256 x 512 rows), 262,144, 524,176 and 1,048,576 rows."""
     p = workloads.Problem("sq", workloads.convdiff_2d(m, pe=40.0), None, None, None, n, 1e-8, 20000)
     g = np.random.default_rng(m)
     p.b = p.A @ g.standard_normal(m * m)
