@@ -201,7 +201,7 @@ def mlbicgstab_solve(h, b_ptr: int, x_ptr: int, q_ptr: int, ldq: int) -> mlb_res
 
 
 def mlbicgstab_solve_batch(handles, b_ptrs, x_ptrs, q_ptrs, ldqs):
-    """One launch for all systems (one workgroup each); returns the list of mlb_result."""
+    """One launch for all systems (a group of workgroups each); returns the list of mlb_result."""
     k = len(handles)
     hs = (mlb_handle * k)(*handles)
     ptrs = lambda v: (ctypes.c_void_p * k)(*[ctypes.c_void_p(p) for p in v])

@@ -21,6 +21,7 @@
 #include <cmath>
 #include <condition_variable>
 #include <deque>
+#include <future>
 #include <mutex>
 #include <thread>
 #include <unordered_map>
@@ -247,8 +248,8 @@ static int device_cus() {
 }
 
 // The ILU(0) factor of A, its conjugate transpose and the rows of the four
-// triangular solves in level order (L, U of the factor; U^H, L^H of its
-// transpose).
+// triangular solves in the order they take the rows (L, U of the factor; U^H, L^H
+// of its transpose).
 template <class V>
 struct IluFactor {
   int bs = 1, nbrows = 0;
@@ -343,6 +344,19 @@ static std::vector<int4> level_rows(const std::vector<int>& rp, const std::vecto
   bchunk.push_back((int)cstart.size());
   cstart.push_back((int)m);
   return out;
+}
+
+// The order of one triangular solve: rows by level, and the rows and chunks in solve order.
+struct IluOrder {
+  std::vector<int> ord, ptr, cstart, bchunk;
+  std::vector<int4> lv;
+};
+
+static IluOrder ilu_order(const std::vector<int>& rp, const std::vector<int>& ci, bool lower, int block) {
+  IluOrder o;
+  level_sets(rp, ci, lower, o.ord, o.ptr);
+  o.lv = level_rows(rp, ci, o.ord, o.ptr, lower, block, o.cstart, o.bchunk);
+  return o;
 }
 
 // One triangular solve in one launch (k_ilu_solve_block); `which` picks its claim counter.
@@ -470,22 +484,19 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   // level sets of the factor's solves (and of the factorisation, the same as L's)
   const std::vector<int> hrp = to_host(A.rp, (size_t)m + 1, s);
   const std::vector<int> hci = to_host(ci, (size_t)A.nnz, s);
-  std::vector<int> ord;
-  level_sets(hrp, hci, true, ord, f.ptrL);
-  f.ordL = al.get<int>(m);
-  HIP_TRY(hipMemcpyAsync(f.ordL, ord.data(), sizeof(int) * m, hipMemcpyHostToDevice, s));
-  std::vector<int> ordU, ptrU;
-  level_sets(hrp, hci, false, ordU, ptrU);
   const int w = ilu_width(A.nnz, m);
   f.block = ilu_block_rows(m);
   f.lds = ilu_lds(bs, (int)sizeof(V) / 8, w);
   if (bs == 1) ilu_allow_lds<V, 1>((int)f.lds.bytes);
   else ilu_allow_lds<V, 3>((int)f.lds.bytes);
-  // the rows of a solve with factor matrix M (index arrays mrp, mci on the host)
-  auto rows = [&](IluRows<V>& r, const std::vector<int>& mrp, const std::vector<int>& mci, const std::vector<int>& o,
-                  const std::vector<int>& ptr, bool lower, bool diag) {
-    std::vector<int> cstart, bchunk;
-    const std::vector<int4> lv = level_rows(mrp, mci, o, ptr, lower, f.block, cstart, bchunk);
+  // the solve orders of a matrix's lower and upper solves (index arrays on the host), side by
+  // side: each is one long scan of the pattern
+  auto orders = [&](const std::vector<int>& mrp, const std::vector<int>& mci, IluOrder& lo, IluOrder& up) {
+    auto other = std::async(std::launch::async, [&] { up = ilu_order(mrp, mci, false, f.block); });
+    lo = ilu_order(mrp, mci, true, f.block);
+    other.get();
+  };
+  auto rows = [&](IluRows<V>& r, const IluOrder& o, bool diag) {
     r.w = w;
     r.lv = al.get<int4>(m);
     r.src = al.get<int>(m);
@@ -493,11 +504,11 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
     r.pc = al.get<int>((size_t)m * w);
     r.pv = al.get<V>((size_t)m * w * b2);
     if (diag) r.pd = al.get<V>((size_t)m * b2);
-    r.cstart = al.get<int>(cstart.size());
-    r.bchunk = al.get<int>(bchunk.size());
-    HIP_TRY(hipMemcpyAsync(r.lv, lv.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(r.cstart, cstart.data(), sizeof(int) * cstart.size(), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(r.bchunk, bchunk.data(), sizeof(int) * bchunk.size(), hipMemcpyHostToDevice, s));
+    r.cstart = al.get<int>(o.cstart.size());
+    r.bchunk = al.get<int>(o.bchunk.size());
+    HIP_TRY(hipMemcpyAsync(r.lv, o.lv.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(r.cstart, o.cstart.data(), sizeof(int) * o.cstart.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(r.bchunk, o.bchunk.data(), sizeof(int) * o.bchunk.size(), hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));   // the host vectors are copied before they go
   };
   auto pack = [&](const Mat<V>& M, const V* dinv, const IluRows<V>& r, const IluRows<V>* before) {
@@ -505,8 +516,13 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
     if (bs == 1) k_ilu_pack<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(M.ci, M.val, dinv, r, m, f.block, f.lds.safe, !before);
     else k_ilu_pack<V, 3><<<grid_for(m, 4096), BLOCK, 0, s>>>(M.ci, M.val, dinv, r, m, f.block, f.lds.safe, !before);
   };
-  rows(f.rowsL, hrp, hci, ord, f.ptrL, true, false);
-  rows(f.rowsU, hrp, hci, ordU, ptrU, false, true);
+  IluOrder lo, up;
+  orders(hrp, hci, lo, up);
+  rows(f.rowsL, lo, false);
+  rows(f.rowsU, up, true);
+  f.ptrL = lo.ptr;
+  f.ordL = al.get<int>(m);
+  HIP_TRY(hipMemcpyAsync(f.ordL, lo.ord.data(), sizeof(int) * m, hipMemcpyHostToDevice, s));
   // factorisation, one launch per level of L
   for (size_t l = 0; l + 1 < f.ptrL.size(); ++l) {
     const int c = f.ptrL[l + 1] - f.ptrL[l];
@@ -529,11 +545,9 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   if (hb & 2) throw Error{MLB_EINVAL, "ILU(0): a zero or singular pivot"};
   const std::vector<int> hrpH = to_host(f.FH.rp, (size_t)m + 1, s);
   const std::vector<int> hciH = to_host(f.FH.ci, (size_t)A.nnz, s);
-  std::vector<int> ordHf, ordHb, ptrHf, ptrHb;
-  level_sets(hrpH, hciH, true, ordHf, ptrHf);
-  level_sets(hrpH, hciH, false, ordHb, ptrHb);
-  rows(f.rowsHf, hrpH, hciH, ordHf, ptrHf, true, true);
-  rows(f.rowsHb, hrpH, hciH, ordHb, ptrHb, false, false);
+  orders(hrpH, hciH, lo, up);   // lo.ord was copied before the synchronisation above
+  rows(f.rowsHf, lo, true);
+  rows(f.rowsHb, up, false);
   pack(f.F, f.dinv, f.rowsL, nullptr);   // lower solves first
   pack(f.F, f.dinv, f.rowsU, &f.rowsL);
   pack(f.FH, f.dinvH, f.rowsHf, nullptr);
@@ -2313,7 +2327,7 @@ struct Request {
   int rc = 0;
   std::string err;
   bool done = false;
-  bool small = false;   // solved by a batcher (one workgroup per system)
+  bool small = false;   // solved by a batcher (many systems in one launch)
   std::shared_ptr<SeqEntry> seq;   // the sequence it belongs to, or null
   int32_t n_used = 0;              // shadow vectors it ran with
 };
@@ -2533,7 +2547,7 @@ static void worker_main(Server* S) {
 
 // A batcher takes every waiting small request that fits the budget (FIFO, at
 // most BATCH_CAP), prepares each on its stream (validation, A^H, workspace),
-// solves them all in one launch of the one-workgroup kernel and completes them
+// solves them all in one launch (batch_impl) and completes them
 // together.  Requests that arrive meanwhile wait for the next batch of the
 // next free batcher.
 constexpr int BATCH_CAP = 256;
