@@ -501,7 +501,7 @@ def main():
     ap.add_argument("--inflight", type=int, default=8, help="serving: solves in flight")
     ap.add_argument("--budget-gb", type=float, default=64.0, help="serving: HBM admission budget")
     ap.add_argument("--small-n-max", type=int, default=0,
-                    help="serving: largest N batched in one-workgroup launches (0 = library default, -1 = none)")
+                    help="serving: largest N solved in batched launches (0 = library default, -1 = none)")
     ap.add_argument("--serve-order", default="fifo", choices=["fifo", "smallest"],
                     help="serving: the workers' pick order (smallest: smallest footprint first, 1 s max wait)")
     ap.add_argument("--serve-precision", default="ir", choices=["fp64", "ir"],

@@ -163,8 +163,8 @@ typedef struct {
  * residual is below tol.  res->iter counts every iteration, res->outer_iters
  * the restarts; iterates are recorded by the first run only.
  * mlbicgstab_solve_batch refuses it; the server runs a small request on its
- * batched one-workgroup solve first and, if that leaves the true residual
- * not below tol, restarts it from its x on the multi-launch iteration.  Not
+ * batched solve first and, if that leaves the true residual not below tol,
+ * restarts it from its x in a solve of its own.  Not
  * taken by MLB_PREC_FP32_IR, whose refinement already tests the true
  * residual.
  */
