@@ -762,11 +762,11 @@ struct Engine {
     st = al.get<State<Sc>>(1);
     part = al.get<Sc>((size_t)MAX_PARTIAL_ROWS * (NMAX + 1));
     part2 = al.get<Sc>((size_t)PSUM_GRID * (NMAX + 1));
+    own_flag = ext_flag == nullptr;   // set_n's routes depend on it
     set_n(n_alloc);
     if (poll) return;   // no host-mapped flag, no events
     if (ext_flag) {
       host_done = ext_flag;
-      own_flag = false;
     } else {
       HIP_TRY(hipHostMalloc((void**)&host_done, sizeof(int), hipHostMallocMapped));
     }
@@ -841,8 +841,8 @@ struct Engine {
     // A server worker's request (it has the worker's flag) whose group would hold every
     // workgroup slot of the card, beyond (GRID_MAX_P - 1) GB = 130,560 rows, is iterated by
     // launches, which run beside those of other requests: groups of that size run one after
-    // the other.  800 requests of 1e3 to 5e5 rows, 8 at a time, solves/s: 259 (fp32 refinement
-    // 128), against 224 (113) with every request solved in one launch and 255 (127) with none.
+    // the other.  500 requests of 1e3 to 5e5 rows, 8 at a time, solves/s: 282 (fp32 refinement
+    // 148), against 212 (113) with every request solved in one launch and 223 (124) with none.
     if (!own_flag && P == GRID_MAX_P) return;
     const int R = (int)(((long long)N + P - 1) / P + WAVE - 1) / WAVE * WAVE;
     if (R > grid_max_rows<V>() / (A.format == MLB_BSR3 ? 2 : 1)) return;
