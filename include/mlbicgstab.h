@@ -200,7 +200,9 @@ typedef struct {
  * With transpose_free neither A^H nor f_1..f_{n-1} is made ((3n+5) N values,
  * Table 4.2).
  * hip_stream: a hipStream_t (NULL = default stream).  On success *out holds
- * the handle; on error *out is NULL.
+ * the handle; on error *out is NULL.  On the default stream solves of up to
+ * 1,048,576 rows run in one launch, on any other those of up to 65,536: larger
+ * ones share the card better as many launches.  The two agree to rounding.
  */
 int mlbicgstab_create(const mlb_matrix* A, const mlb_options* opt, void* hip_stream, mlb_handle* out);
 
@@ -435,8 +437,9 @@ int mlb_server_wait(mlb_server_handle s, int64_t ticket, mlb_result* res, mlb_re
  * The first request runs with opt->n; after each request the next n follows
  * mlb_sequence_next_n with the solve times of the previous and the current
  * request (timing->n_used reports it).  Each result is bitwise that of a fresh
- * create + solve with that n.  Q is N x n_max (column-major, ldq >= N), of
- * which the first n columns are used.  The sequence's footprint
+ * create + solve with that n on a stream other than the default one.
+ * Q is N x n_max (column-major, ldq >= N), of which the first n columns are
+ * used.  The sequence's footprint
  * (mlbicgstab_workspace_size with n = n_max) is admitted with its first
  * request and held until mlb_server_end_sequence; other requests keep flowing
  * meanwhile.  Errors as mlb_server_submit; MLB_EINVAL for key 0, for an A,

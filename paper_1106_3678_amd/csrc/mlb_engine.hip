@@ -737,8 +737,9 @@ struct Engine {
   // 154 VGPRs in the alpha pass.
   bool s_alpha = false;
   // Whole solves in one launch (mlb_grid.hpp): workgroups and rows per workgroup, 0:
-  // the multi-launch iteration.  Set by set_n.
+  // the multi-launch iteration; grid_solo: solve() takes it (a batch always does).  Set by set_n.
   int grid_P = 0, grid_R = 0, grid_cap = 0;
+  bool grid_solo = false;
   unsigned grid_max_tries = ~0u;
   long long grid_entry_ticks = GRID_ENTRY_TICKS;
 
@@ -838,18 +839,25 @@ struct Engine {
     grid_P = 0;
     if (literal || ilu) return;
     const int P = std::min(GRID_MAX_P, (int)(((long long)N + GB - 1) / GB));
-    // A server worker's request (it has the worker's flag) whose group would hold every
-    // workgroup slot of the card, beyond (GRID_MAX_P - 1) GB = 130,560 rows, is iterated by
-    // launches, which run beside those of other requests: groups of that size run one after
-    // the other.  500 requests of 1e3 to 5e5 rows, 8 at a time, solves/s: 282 (fp32 refinement
-    // 148), against 212 (113) with every request solved in one launch and 223 (124) with none.
-    if (!own_flag && P == GRID_MAX_P) return;
     const int R = (int)(((long long)N + P - 1) / P + WAVE - 1) / WAVE * WAVE;
     if (R > grid_max_rows<V>() / (A.format == MLB_BSR3 ? 2 : 1)) return;
     grid_R = R;
     grid_cap = grid_capacity<V>(nb, A.format == MLB_BSR3, grid_kr());
     grid_P = (N + R - 1) / R;
     if (grid_P > grid_cap) grid_P = 0;
+    // On a stream of its own other solves may run beside this one, and a group that leaves no
+    // room on the card for a second one would run after the others' instead.  So solve()
+    // iterates by launches there beyond half the CUs, 65,536 rows; ms a solve (n = 4) by
+    // launches / whole with 4 threads: 1.63 / 2.23 at 103,823 rows, 3.4 / 4.8 at 250,047, 6.7 /
+    // 9.1 at 512,000 (fp32 2.7 / 3.8, 4.5 / 7.2, 8.5 / 12.7), where one alone takes 4.6 / 2.3,
+    // 7.5 / 4.8, 12.3 / 9.1; 1.2 / 0.95 at 64,000 rows, where two groups fit.  A server worker
+    // (it lends the flag) mixes sizes, and groups of up to GRID_MAX_P - 1 slices, 130,560 rows,
+    // fill what the other requests leave: 800 requests of 1e3 to 5e5 rows, 8 at a time, solves/s
+    // 291 (fp32 refinement 171) against 293 (149) with the line at half the CUs and 258 (134)
+    // without any whole solves.  The stream alone decides, not what runs on others, so
+    // a solve's result does not depend on that.
+    const int room = s == nullptr || s == hipStreamLegacy ? GRID_MAX_P : own_flag ? device_cus() / 2 : GRID_MAX_P - 1;
+    grid_solo = P <= room;
     // test hooks, read from the environment: a wait that gives up after so many tries (its solve
     // fails with MLB_EHIP), and the time a group waits at its gate (0: it mostly leaves)
     if (const char* e = std::getenv("MLB_GRID_MAX_TRIES")) {
@@ -1213,7 +1221,7 @@ struct Engine {
   // Algorithm 7.1 with M = I from x (in: x_0, out: solution).
   Out solve(const V* b, V* x, const V* Q_, long long ldq_, double tol, long long maxit, double kappa, V* xrec,
             long long K, long long stag_window = 0, bool resid = false) {
-    if (grid_P) {
+    if (grid_P && grid_solo) {
       Q = Q_;
       ldq = ldq_;
       GridOut g{};
