@@ -133,6 +133,7 @@ struct Mat {
   const int* ci = nullptr;
   const V* val = nullptr;
   int lpr = 8;         // lanes per (block) row in the SpMV tile
+  int longest = 0;     // entries of the longest (block) row
 };
 
 static int pick_lpr(long long nnz, int nbrows) {
@@ -144,15 +145,18 @@ static int pick_lpr(long long nnz, int nbrows) {
 }
 
 // Checks row_ptr / col_idx of a user matrix on the device (so that no kernel
-// ever indexes outside the arrays the descriptor declares).
+// ever indexes outside the arrays the descriptor declares), and finds its longest row.
 __global__ void k_validate(const int* __restrict__ rp, const int* __restrict__ ci, int nbrows, long long nnz,
-                           int ncols, int* __restrict__ bad) {
+                           int ncols, int* __restrict__ bad, int* __restrict__ longest) {
+  int len = 0;
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t <= nbrows; t += (long long)gridDim.x * blockDim.x) {
     const int v = rp[t];
     if (t == 0 && v != 0) atomicOr(bad, 1);
     if (t == nbrows && (long long)v != nnz) atomicOr(bad, 2);
     if (t < nbrows && rp[t + 1] < v) atomicOr(bad, 4);
+    if (t < nbrows) len = max(len, rp[t + 1] - v);
   }
+  note_longest(len, longest);
   for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < nnz; q += (long long)gridDim.x * blockDim.x) {
     const int c = ci[q];
     if (c < 0 || c >= ncols) atomicOr(bad, 8);
@@ -190,14 +194,17 @@ static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s) {
     k_scan_sums<<<1, SCAN_T, 0, s>>>(tsum, ntiles);
     k_scan_apply<<<ntiles, SCAN_T, 0, s>>>(cnt, m, tsum, ntiles, rpT);
   }
+  int* longest = cnt;   // the counts are used up
+  k_fill<int><<<1, BLOCK, 0, s>>>(longest, 1, 0);
   if (bs == 1) {
     k_scatter<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(A.rp, A.ci, A.val, m, rpT, fill, ciT, valT);
-    k_sort_rows<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT);
+    k_sort_rows<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT, longest);
   } else {
     k_scatter<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(A.rp, A.ci, A.val, m, rpT, fill, ciT, valT);
-    k_sort_rows<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT);
+    k_sort_rows<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT, longest);
   }
   HIP_TRY(hipGetLastError());
+  HIP_TRY(hipMemcpyAsync(&T.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));   // tmp_own is freed on return
   T.rp = rpT;
   T.ci = ciT;
@@ -824,6 +831,21 @@ struct Engine {
     pick_grid();
   }
 
+  // A whole solve walks a row with one lane, the multi-launch products one of more than 8
+  // entries with 16 or 32, so solve() takes the launches where a lane has much to walk.  us an
+  // iteration, launches / whole, random patterns, n = 4: entries a lane walks in a product
+  // (a row's times rows a lane) 40: 104 / 87 (130,000 rows), 46: 112 / 97 (500,000), 48: 98 / 104
+  // (260,000), 62: 131 / 137 (500,000); complex 24: 91 / 85 (260,000), 32: 101 / 107, 35: 140 /
+  // 139 (500,000), 46: 162 / 175; fp32 62: 154 / 127 (500,000), 80: 173 / 217 (260,000), 93: 198 /
+  // 213, but 8 rows of 12 217 / 194 (1,000,000); 3x3 blocks 20: 61 / 57 (258,000), 28: 74 / 83 (510,000).  One long row among
+  // 100,000 of five: 96 entries 39 / 33, 192 44 / 49, 1,024 87 / 184.  A long row of A^H
+  // is walked n - 1 times a solve.
+  bool rows_suit_grid() const {
+    const bool blocks = A.format == MLB_BSR3;
+    const double row = (double)A.nnz / A.nbrows, walk = row * std::max(1.0, (double)grid_R / GB);
+    const double most = blocks ? (sizeof(V) > 8 ? 16 : 27) : sizeof(V) > 8 ? 31 : sizeof(V) > 4 ? 47 : row > 12 ? 64 : 96;
+    return walk <= most && A.longest <= (blocks ? 48 : 96) && (long long)AH.longest * (n - 1) <= 4096;
+  }
   bool grid_kr() const { return grid_R <= GB && grid_keeps_rows<V>(nb); }
   // Whole solves in one launch up to GRID_MAX_P slices of grid_max_rows rows (1,048,576
   // rows; complex 524,288; half of that for 3x3 blocks), for everything but the literal
@@ -857,7 +879,7 @@ struct Engine {
     // without any whole solves.  The stream alone decides, not what runs on others, so
     // a solve's result does not depend on that.
     const int room = s == nullptr || s == hipStreamLegacy ? GRID_MAX_P : own_flag ? device_cus() / 2 : GRID_MAX_P - 1;
-    grid_solo = P <= room;
+    grid_solo = P <= room && rows_suit_grid();
     // test hooks, read from the environment: a wait that gives up after so many tries (its solve
     // fails with MLB_EHIP), and the time a group waits at its gate (0: it mostly leaves)
     if (const char* e = std::getenv("MLB_GRID_MAX_TRIES")) {
@@ -1376,6 +1398,7 @@ struct mlb_solver {
   int* ext_flags = nullptr;   // two pinned host-mapped ints owned by a serving worker, or NULL
   bool noalloc = false;       // everything in the caller's arena, no host-mapped flags or events
   int n_active = 0;           // shadow vectors of the next solve (<= opt.n, the workspace's)
+  int longest = 0;            // entries of A's longest (block) row
   Allocs al;
   std::unique_ptr<Impl<double, float>> real;
   std::unique_ptr<Impl<cplx<double>, cplx<float>>> cpx;
@@ -1447,6 +1470,7 @@ static Mat<V> user_matrix(const mlb_matrix* A) {
 template <class V64, class V32>
 static void create_impl(mlb_solver* h, const mlb_matrix* Adesc, Impl<V64, V32>& im) {
   Mat<V64> A = user_matrix<V64>(Adesc);
+  A.longest = h->longest;
   if (A.nnz == 0) {
     // no entries: the caller may pass NULL index / value arrays; give the kernels
     // valid (never read) ones instead
@@ -1520,6 +1544,8 @@ static void create_impl(mlb_solver* h, const mlb_matrix* Adesc, Impl<V64, V32>& 
     AH32.val = vt;
     A32.lpr = A.lpr;
     AH32.lpr = AH.lpr;
+    A32.longest = A.longest;
+    AH32.longest = AH.longest;
     im.e32.tf = tf;
     im.e32.literal = h->opt.order == MLB_ORDER_LITERAL;
     im.e32.init(A32, AH32, h->opt.n, h->s, h->al, h->ext_flags ? h->ext_flags + 1 : nullptr);
@@ -1839,15 +1865,17 @@ static std::unique_ptr<mlb_solver> create_solver(const mlb_matrix* A, const mlb_
   {
     Allocs tmp_own(stream, ordered);
     Allocs& tmp = h->noalloc ? h->al : tmp_own;
-    int* bad = tmp.get<int>(1);
-    k_fill<int><<<1, BLOCK, 0, h->s>>>(bad, 1, 0);
+    int* bad = tmp.get<int>(2);   // what is wrong, entries of the longest row
+    k_fill<int><<<1, BLOCK, 0, h->s>>>(bad, 2, 0);
     const int nbr = A->format == MLB_BSR3 ? (int)(A->nrows / 3) : (int)A->nrows;
     k_validate<<<grid_for(std::max<long long>(nbr + 1, A->nnz), 4096), BLOCK, 0, h->s>>>(A->row_ptr, A->col_idx, nbr,
-                                                                                         A->nnz, nbr, bad);
+                                                                                         A->nnz, nbr, bad, bad + 1);
     HIP_TRY(hipGetLastError());
-    int hb = 0;
-    HIP_TRY(hipMemcpyAsync(&hb, bad, sizeof(int), hipMemcpyDeviceToHost, h->s));
+    int seen[2] = {0, 0};
+    HIP_TRY(hipMemcpyAsync(seen, bad, sizeof(seen), hipMemcpyDeviceToHost, h->s));
     HIP_TRY(hipStreamSynchronize(h->s));
+    const int hb = seen[0];
+    h->longest = seen[1];
     if (hb) {
       std::string why;
       if (hb & 1) why += " row_ptr[0] != 0;";
@@ -2261,7 +2289,7 @@ static size_t noalloc_bytes_t(const mlb_matrix* A, const mlb_options* opt) {
   const size_t bs = bsr ? 9 : 1;
   const size_t nnz = (size_t)A->nnz;
   const bool tf = opt->transpose_free != 0;
-  size_t t = arena_bytes<int>(1);                                   // index check flag
+  size_t t = arena_bytes<int>(2);                                   // index check flag, longest row
   if (nnz == 0) t += arena_bytes<int>(1) + arena_bytes<V>(bs);       // stand-in index / value arrays
   if (!tf) {
     t += arena_bytes<int>(m + 1) + arena_bytes<int>(nnz) + arena_bytes<V>(nnz * bs);   // A^H
