@@ -117,8 +117,9 @@ typedef struct {
  * copy of A's index arrays) and fails with MLB_EINVAL for a (block) row without
  * a stored diagonal, a column stored twice in a row, or a zero / singular
  * pivot.  Each triangular solve is one launch, a workgroup per block of
- * consecutive rows, every row waiting for the solved values it reads (3m - 2
- * dependent levels on an m^3 7-point grid); a wait is bounded (2 s), and a solve
+ * consecutive rows (or, where most entries lead out of a block or the rows are
+ * long, the rows dealt out level by level), every row waiting for the solved
+ * values it reads (3m - 2 dependent levels on an m^3 7-point grid); a wait is bounded (2 s), and a solve
  * in which one ran out returns MLB_EHIP (the environment variable
  * MLB_ILU_MAX_TRIES, read by create(), bounds the tries of a wait instead: a test
  * hook for that path).

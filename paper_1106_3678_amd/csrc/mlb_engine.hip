@@ -273,6 +273,8 @@ struct IluFactor {
   unsigned* ctl = nullptr;            // one-launch solves: claim counters [0] and [1], lost-wait flag [2]
   int block = 1;                      // (block) rows of a workgroup
   IluLds lds;                         // and how it uses its LDS
+  bool blocksF = true, blocksH = true;   // the two solves of F / of FH go by blocks of rows, else by level
+  int sweep_grid = 1;                 // workgroups of a solve by level (each wave claims until none are left)
   unsigned max_tries = ~0u;           // tries of a row before it gives up (MLB_ILU_MAX_TRIES, for tests)
 };
 
@@ -311,59 +313,99 @@ static IluLds ilu_lds(int bs, int words, int w) {
 
 static int ilu_width(long long nnz, int m);
 
+// Waves of a solve by level, as a multiple of the waves one average level fills
+// (capped at two per CU), one wave per workgroup so that they spread over the CUs.
+static constexpr double ILU_SWEEP_LEVEL_MULT = 3.0;
+
 static int level_grid(int count) { return std::max(1, std::min((count + BLOCK - 1) / BLOCK, 4096)); }
 
-// The rows of a solve in solve order with their entry ranges (host): {i, q0, q1, 0},
-// [q0, q1) the stored entries left (lower) or right of row i's diagonal.  Every row
-// has a stored diagonal (checked before).  ord: the rows by level; the solve order is by
-// block, first from the first row (lower) or the last, and by level inside a block.
-// cstart, bchunk: the chunks (see IluRows); ptr: the level pointers of ord.
-static std::vector<int4> level_rows(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<int>& ord,
-                                    const std::vector<int>& ptr, bool lower, int block, std::vector<int>& cstart,
-                                    std::vector<int>& bchunk) {
-  const size_t m = ord.size();
-  std::vector<int> lev(m);   // level of every position
+// The stored entries [q0, q1) left (lower) or right of row i's diagonal (every row has one,
+// checked before), as {i, q0, q1, 0}.
+static int4 ilu_row(const std::vector<int>& rp, const std::vector<int>& ci, int i, bool lower) {
+  int qd = rp[i];
+  for (int q = rp[i]; q < rp[i + 1]; ++q)
+    if (ci[q] == i) {
+      qd = q;
+      break;
+    }
+  return make_int4(i, lower ? rp[i] : qd + 1, lower ? qd : rp[i + 1], 0);
+}
+
+// The order of one triangular solve (host).  lv: the rows in solve order: by block, first from
+// the first row (lower) or the last, and by level inside a block.  Over every ILU_SAMPLE-th row
+// (by level), rows: how many, side: their entries, far: those that a block reads from memory,
+// loose: those beyond the w packed ones.
+constexpr int ILU_SAMPLE = 4;
+struct IluOrder {
+  std::vector<int> ord, ptr, cstart, bchunk;   // rows by level, level pointers, chunks (see IluRows)
+  std::vector<int4> lv;
+  long long rows = 0, side = 0, far = 0, loose = 0;
+};
+
+static IluOrder ilu_order(const std::vector<int>& rp, const std::vector<int>& ci, bool lower, int block, int w,
+                          int safe) {
+  IluOrder o;
+  level_sets(rp, ci, lower, o.ord, o.ptr);
+  const size_t m = o.ord.size();
+  std::vector<int> lev(m), pos(m);   // level of every position, position of every row
   size_t level = 0;
-  std::vector<int4> out(m);
+  o.lv.resize(m);
   std::vector<int> fill((m + block - 1) / block);
   for (size_t k = 0; k < fill.size(); ++k) fill[k] = (int)(k * block);
   for (size_t r = 0; r < m; ++r) {
-    const int i = ord[r];
-    while ((int)r >= ptr[level + 1]) ++level;
-    const int t = fill[(lower ? (size_t)i : m - 1 - i) / block]++;
+    const int i = o.ord[r];
+    while ((int)r >= o.ptr[level + 1]) ++level;
+    const size_t k = (lower ? (size_t)i : m - 1 - i) / block;
+    const int t = fill[k]++;
     lev[t] = (int)level;
-    int qd = rp[i];
-    for (int q = rp[i]; q < rp[i + 1]; ++q)
-      if (ci[q] == i) {
-        qd = q;
-        break;
-      }
-    out[t] = make_int4(i, lower ? rp[i] : qd + 1, lower ? qd : rp[i + 1], 0);
+    pos[i] = t;
+    const int4 row = o.lv[t] = ilu_row(rp, ci, i, lower);
+    if (r % ILU_SAMPLE) continue;
+    ++o.rows;
+    o.side += row.z - row.y;
+    o.loose += std::max(0, row.z - row.y - w);
+    for (int q = row.y; q < row.z; ++q) {   // its row is of an earlier level
+      const int tj = pos[ci[q]];
+      o.far += tj < (int)(k * block) || t - tj > safe;
+    }
   }
   // chunks: at most 64 positions of one level of one block
-  cstart.clear();
-  bchunk.assign(1, 0);
+  o.bchunk.assign(1, 0);
   for (size_t t = 0; t < m; ++t)
-    if (t % block == 0 || lev[t] != lev[t - 1] || (int)t - cstart.back() == WAVE) {
-      if (t && t % block == 0) bchunk.push_back((int)cstart.size());
-      cstart.push_back((int)t);
+    if (t % block == 0 || lev[t] != lev[t - 1] || (int)t - o.cstart.back() == WAVE) {
+      if (t && t % block == 0) o.bchunk.push_back((int)o.cstart.size());
+      o.cstart.push_back((int)t);
     }
-  bchunk.push_back((int)cstart.size());
-  cstart.push_back((int)m);
-  return out;
+  o.bchunk.push_back((int)o.cstart.size());
+  o.cstart.push_back((int)m);
+  return o;
 }
 
-// The order of one triangular solve: rows by level, and the rows and chunks in solve order.
-struct IluOrder {
-  std::vector<int> ord, ptr, cstart, bchunk;
-  std::vector<int4> lv;
-};
+// Whether the two solves of a matrix go by blocks of rows, else by level.  Blocks win where
+// almost all of a row's values come from the block's own ring in LDS; values from memory cost
+// a workgroup's loaders what the whole card shares in a solve by level.  us for both solves,
+// by level / by blocks (real values): 7 points 32^3 312 / 160, 64^3 641 / 322; 9 points 256^2
+// 2,064 / 781; a band of 2 / 4 entries a side 34.9 / 16.6 ms, 5 (one beyond the packed 4) 48.6
+// / 39.9, 20 237 / 207; loose entries a row 0.18: 11.5 / 5.2 ms, but 0.27: 13.7 / 13.9, 0.33: 6.6 /
+// 9.2, 0.42 (a triangulation of 200,000 points) 2.9 / 4.7, 0.78 (7 points 48^3 in random order)
+// 128 / 438 us, 27 points 32^3 1.6 / 3.1 ms, 12 random entries a row (200,000 rows) 0.23 / 1.5.
+// Far entries: 0.13 of them at 64^3 in natural order, all red-black 148 / 282, all of a matrix
+// with two diagonals 9,000 off 125 / 372.  A band's levels are one row, so its chain is
+// what bounds it and the packed entries still pay.
+static bool ilu_by_blocks(const IluOrder& lo, const IluOrder& up) {
+  const double side = (double)(lo.side + up.side), rows = (double)(lo.rows + up.rows);
+  const double levels = (double)(lo.ptr.size() + up.ptr.size() - 2);
+  const bool narrow = (double)(lo.ord.size() + up.ord.size()) <= 2.0 * levels;
+  return lo.far + up.far <= 0.4 * side && (lo.loose + up.loose <= 0.2 * rows || narrow);
+}
 
-static IluOrder ilu_order(const std::vector<int>& rp, const std::vector<int>& ci, bool lower, int block) {
-  IluOrder o;
-  level_sets(rp, ci, lower, o.ord, o.ptr);
-  o.lv = level_rows(rp, ci, o.ord, o.ptr, lower, block, o.cstart, o.bchunk);
-  return o;
+// One triangular solve in one launch by level (k_ilu_solve_sweep); `which` picks its claim counter.
+template <class V, int BS, bool LOWER, bool UNIT>
+static void ilu_sweep1(const IluFactor<V>& f, const Mat<V>& M, const V* dinv, const IluRows<V>& rows, const V* in,
+                       V* out, V* next, int which, hipStream_t s, const int* done) {
+  k_ilu_solve_sweep<V, BS, LOWER, UNIT><<<f.sweep_grid, WAVE, 0, s>>>(M.ci, M.val, dinv, rows.lv, f.nbrows, in, out,
+                                                                       next, f.ctl + which, f.ctl + 2, f.max_tries,
+                                                                       done);
 }
 
 // One triangular solve in one launch (k_ilu_solve_block); `which` picks its claim counter.
@@ -397,7 +439,15 @@ static void ilu_apply(const IluFactor<V>& f, const V* in, V* out, hipStream_t s,
     throw Error{MLB_EUNSUPPORTED, "ILU(0) runs on fp64 values only"};
   } else {
     ilu_pending(f, s, done);
-    if (f.bs == 1) {
+    if (!f.blocksF) {
+      if (f.bs == 1) {
+        ilu_sweep1<V, 1, true, true>(f, f.F, f.dinv, f.rowsL, in, f.tmid, out, 0, s, done);
+        ilu_sweep1<V, 1, false, false>(f, f.F, f.dinv, f.rowsU, f.tmid, out, nullptr, 1, s, done);
+      } else {
+        ilu_sweep1<V, 3, true, true>(f, f.F, f.dinv, f.rowsL, in, f.tmid, out, 0, s, done);
+        ilu_sweep1<V, 3, false, false>(f, f.F, f.dinv, f.rowsU, f.tmid, out, nullptr, 1, s, done);
+      }
+    } else if (f.bs == 1) {
       ilu_solve1<V, 1, true, true>(f, f.F, f.rowsL, in, f.tmid, nullptr, f.tend, 0, s, done);
       ilu_solve1<V, 1, false, false>(f, f.F, f.rowsU, f.tmid, f.tend, out, nullptr, 1, s, done);
     } else {
@@ -414,7 +464,15 @@ static void ilu_apply_h(const IluFactor<V>& f, V* v, hipStream_t s, const int* d
     throw Error{MLB_EUNSUPPORTED, "ILU(0) runs on fp64 values only"};
   } else {
     ilu_pending(f, s, done);
-    if (f.bs == 1) {
+    if (!f.blocksH) {
+      if (f.bs == 1) {
+        ilu_sweep1<V, 1, true, false>(f, f.FH, f.dinvH, f.rowsHf, v, f.tmid, v, 0, s, done);
+        ilu_sweep1<V, 1, false, true>(f, f.FH, f.dinvH, f.rowsHb, f.tmid, v, nullptr, 1, s, done);
+      } else {
+        ilu_sweep1<V, 3, true, false>(f, f.FH, f.dinvH, f.rowsHf, v, f.tmid, v, 0, s, done);
+        ilu_sweep1<V, 3, false, true>(f, f.FH, f.dinvH, f.rowsHb, f.tmid, v, nullptr, 1, s, done);
+      }
+    } else if (f.bs == 1) {
       ilu_solve1<V, 1, true, false>(f, f.FH, f.rowsHf, v, f.tmid, nullptr, f.tend, 0, s, done);
       ilu_solve1<V, 1, false, true>(f, f.FH, f.rowsHb, f.tmid, f.tend, v, nullptr, 1, s, done);
     } else {
@@ -499,9 +557,17 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   // the solve orders of a matrix's lower and upper solves (index arrays on the host), side by
   // side: each is one long scan of the pattern
   auto orders = [&](const std::vector<int>& mrp, const std::vector<int>& mci, IluOrder& lo, IluOrder& up) {
-    auto other = std::async(std::launch::async, [&] { up = ilu_order(mrp, mci, false, f.block); });
-    lo = ilu_order(mrp, mci, true, f.block);
+    auto other = std::async(std::launch::async, [&] { up = ilu_order(mrp, mci, false, f.block, w, f.lds.safe); });
+    lo = ilu_order(mrp, mci, true, f.block, w, f.lds.safe);
     other.get();
+  };
+  auto by_level = [&](IluRows<V>& r, const IluOrder& o, const std::vector<int>& mrp, const std::vector<int>& mci,
+                      bool lower) {
+    std::vector<int4> lv(m);
+    for (int t = 0; t < m; ++t) lv[t] = ilu_row(mrp, mci, o.ord[t], lower);
+    r.lv = al.get<int4>(m);
+    HIP_TRY(hipMemcpyAsync(r.lv, lv.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));   // lv is copied before it goes
   };
   auto rows = [&](IluRows<V>& r, const IluOrder& o, bool diag) {
     r.w = w;
@@ -525,8 +591,16 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   };
   IluOrder lo, up;
   orders(hrp, hci, lo, up);
-  rows(f.rowsL, lo, false);
-  rows(f.rowsU, up, true);
+  f.blocksF = ilu_by_blocks(lo, up);
+  if (f.blocksF) {
+    rows(f.rowsL, lo, false);
+    rows(f.rowsU, up, true);
+  } else {
+    by_level(f.rowsL, lo, hrp, hci, true);
+    by_level(f.rowsU, up, hrp, hci, false);
+  }
+  const double level_waves = (double)m / (double)std::max<size_t>(1, lo.ptr.size() - 1) / WAVE;
+  f.sweep_grid = (int)std::min<double>(2.0 * device_cus(), std::max(1.0, ILU_SWEEP_LEVEL_MULT * level_waves));
   f.ptrL = lo.ptr;
   f.ordL = al.get<int>(m);
   HIP_TRY(hipMemcpyAsync(f.ordL, lo.ord.data(), sizeof(int) * m, hipMemcpyHostToDevice, s));
@@ -553,12 +627,22 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   const std::vector<int> hrpH = to_host(f.FH.rp, (size_t)m + 1, s);
   const std::vector<int> hciH = to_host(f.FH.ci, (size_t)A.nnz, s);
   orders(hrpH, hciH, lo, up);   // lo.ord was copied before the synchronisation above
-  rows(f.rowsHf, lo, true);
-  rows(f.rowsHb, up, false);
-  pack(f.F, f.dinv, f.rowsL, nullptr);   // lower solves first
-  pack(f.F, f.dinv, f.rowsU, &f.rowsL);
-  pack(f.FH, f.dinvH, f.rowsHf, nullptr);
-  pack(f.FH, f.dinvH, f.rowsHb, &f.rowsHf);
+  f.blocksH = ilu_by_blocks(lo, up);
+  if (f.blocksH) {
+    rows(f.rowsHf, lo, true);
+    rows(f.rowsHb, up, false);
+  } else {
+    by_level(f.rowsHf, lo, hrpH, hciH, true);
+    by_level(f.rowsHb, up, hrpH, hciH, false);
+  }
+  if (f.blocksF) {   // lower solves first
+    pack(f.F, f.dinv, f.rowsL, nullptr);
+    pack(f.F, f.dinv, f.rowsU, &f.rowsL);
+  }
+  if (f.blocksH) {
+    pack(f.FH, f.dinvH, f.rowsHf, nullptr);
+    pack(f.FH, f.dinvH, f.rowsHb, &f.rowsHf);
+  }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));   // the host vectors above are copied before they go
 }

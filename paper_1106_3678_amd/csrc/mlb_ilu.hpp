@@ -11,7 +11,7 @@
 // rows k < i of its own pattern, so all the rows of one level (rows whose
 // longest chain of such dependencies has the same length) are factored
 // together, one launch per level.  The triangular solves of M^{-1} v = U^{-1}
-// (L^{-1} v) are one launch each (k_ilu_solve_block), and M^{-H} v = L^{-H}
+// (L^{-1} v) are one launch each (k_ilu_solve_block or k_ilu_solve_sweep), and M^{-H} v = L^{-H}
 // (U^{-H} v) runs on the conjugate transpose of the factor matrix, whose lower
 // part is U^H and whose upper part is L^H.
 //
@@ -131,7 +131,7 @@ __global__ void k_ilu_inv_diag(const V* __restrict__ val, const int* __restrict_
   }
 }
 
-// ---- one launch per triangular solve ---------------------------------------
+// ---- one launch per triangular solve, blocks of rows ------------------------
 //
 // The rows are cut into blocks of consecutive rows, one workgroup each, claimed
 // from a counter in the order of the solve: every block that a claimed one reads
@@ -652,6 +652,197 @@ __global__ __launch_bounds__((ilu_threads<BS>())) void k_ilu_solve_block(
     for (int e = 0; e < BS; ++e) put(f + e * W * WAVE, s[e]);
     order();
     if (lane == 0) __hip_atomic_store(&ready[sl], x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+}
+
+// ---- one launch per triangular solve, rows dealt out one level after the other -----
+//
+// For patterns that blocks of consecutive rows do not suit: entries that mostly lead
+// into other blocks, or rows longer than what is packed, whose values would all come
+// through memory to one workgroup.  Here the rows of the whole solve go through one
+// launch in level order: each wave claims the next 64 positions from a counter, so
+// every position below a claimed one is claimed too, by a wave that is running, and
+// every link of the chain is a store to and a load from memory, 1.5 to 2.1 us.  The
+// lowest position still waiting reads only finished rows, so the solve always moves on;
+// a wave whose lanes wait on each other (a level boundary inside its 64 positions)
+// retries its pending lanes together, so a finished lane stores before the others test
+// again.
+
+// One group of (at most) 4 entries of a row: loads the solved values they
+// reference (entries at u >= cnt repeat the last one, unused) and, when none
+// is pending, subtracts a_u x_u from s in entry order.  Returns false, leaving
+// s as it was, while one is pending; *waitw then holds the address of a
+// pending word.
+template <class V, int BS>
+__device__ inline bool ilu_group(const V (&a)[4][BS * BS], const int (&c)[4], int cnt, unsigned long long* ow,
+                                 V (&s)[BS], unsigned long long** waitw) {
+  constexpr int W = sizeof(V) / 8;
+  using U = unsigned long long;
+  U xw[4][BS * W];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int k = 0; k < BS * W; ++k) xw[u][k] = ilu_ld(ow + (size_t)BS * W * c[u] + k);
+  bool ready = true;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int k = 0; k < BS * W; ++k)
+      if (xw[u][k] == ILU_PENDING) {
+        ready = false;
+        *waitw = ow + (size_t)BS * W * c[u] + k;
+      }
+  if (!ready) return false;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (u < cnt) {
+      V xv[BS];
+#pragma unroll
+      for (int e = 0; e < BS; ++e) __builtin_memcpy(&xv[e], &xw[u][W * e], sizeof(V));
+#pragma unroll
+      for (int r = 0; r < BS; ++r) {
+        V acc = zero<V>();
+#pragma unroll
+        for (int k = 0; k < BS; ++k) acc = axpy(acc, a[u][BS * r + k], xv[k]);
+        s[r] = s[r] - acc;
+      }
+    }
+  return true;
+}
+
+// One triangular solve with a factor matrix, the same arithmetic as one
+// launch per level (the same entries in the same order): LOWER: out_i = in_i -
+// sum_{stored j < i} a_ij out_j, else with the stored j > i; UNIT: that value is
+// out_i, else out_i = a_ii^{-1} (value) (a division for scalars, the stored
+// inverse block dinv for 3x3 blocks).  lv: all m rows in level order, {i, q0,
+// q1, 0} with [q0, q1) the entries left (LOWER) or right of the diagonal.  out
+// must hold the pending mark (k_ilu_pending) and may not overlap in.  next: the
+// output of the solve that follows, or null: row i of it is marked pending
+// once in_i is read (so next may be in).  tick: this solve's claim counter, 0
+// at launch; err: set to 1 when a wait ran past its bound; max_tries: tries of
+// one row before it gives up regardless of time (~0u: no such limit; a small
+// value forces the give-up path in tests).  done: the solve's done flag (the
+// launch returns at once when it is set), or null.
+template <class V, int BS, bool LOWER, bool UNIT>
+__global__ __launch_bounds__(WAVE) void k_ilu_solve_sweep(const int* __restrict__ ci, const V* __restrict__ val,
+                                                          const V* __restrict__ dinv, const int4* __restrict__ lv,
+                                                          int m, const V* in, V* out, V* next, unsigned* tick,
+                                                          unsigned* err, unsigned max_tries, const int* done) {
+  constexpr int B2 = BS * BS;
+  constexpr int W = sizeof(V) / 8;   // 64-bit words per value (1 real, 2 complex)
+  using U = unsigned long long;
+  static_assert(sizeof(V) == 8 * W, "fp64 values only");
+  if (done && *(volatile const int*)done) return;
+  const int lane = threadIdx.x & (WAVE - 1);
+  U* ow = reinterpret_cast<U*>(out);
+  for (;;) {
+    unsigned base = 0;
+    if (lane == 0) base = atomicAdd(tick, (unsigned)WAVE);
+    base = __shfl(base, 0, WAVE);
+    if (base >= (unsigned)m) return;
+    const int t = (int)base + lane;
+    bool pending = t < m;
+    int4 rw = make_int4(0, 0, 0, 0);
+    if (pending) rw = lv[t];
+    const int i = rw.x, q0 = rw.y, q1 = rw.z;
+    V s0[BS];
+#pragma unroll
+    for (int e = 0; e < BS; ++e) s0[e] = pending ? in[(size_t)BS * i + e] : zero<V>();
+    if (pending && next) {
+      U* nw = reinterpret_cast<U*>(next) + (size_t)BS * W * i;
+#pragma unroll
+      for (int k = 0; k < BS * W; ++k) nw[k] = ILU_PENDING;
+    }
+    // the first (at most) 4 entries, held in registers across the tries: most rows
+    // have no more, and a try then reloads only the solved values they reference
+    int c0[4];
+    V a0[4][B2];
+    const bool has0 = pending && q0 < q1;
+    if (has0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = q0 + u < q1 ? q0 + u : q1 - 1;
+        c0[u] = ci[q];
+#pragma unroll
+        for (int e = 0; e < B2; ++e) a0[u][e] = val[(size_t)B2 * q + e];
+      }
+    }
+    // the diagonal (block) inverse's operand, off the waiting path
+    V dg[UNIT ? 1 : (BS == 1 ? 1 : B2)];
+    if constexpr (!UNIT) {
+      if (pending) {
+        if constexpr (BS == 1) {
+          dg[0] = val[LOWER ? q1 : q0 - 1];
+        } else {
+#pragma unroll
+          for (int e = 0; e < B2; ++e) dg[e] = dinv[(size_t)B2 * i + e];
+        }
+      }
+    }
+    const long long t_start = wall_clock64();
+    unsigned tries = 0;
+    U* waitw = nullptr;   // a word the last try found pending: polled alone first
+    while (__any(pending)) {
+      if (pending) {
+        V s[BS];
+#pragma unroll
+        for (int e = 0; e < BS; ++e) s[e] = s0[e];
+        bool ready = !waitw || ilu_ld(waitw) != ILU_PENDING;
+        if (ready) waitw = nullptr;
+        if (ready && has0) ready = ilu_group<V, BS>(a0, c0, q1 - q0, ow, s, &waitw);
+        // further entries in groups of 4, loaded again on every try
+        for (int q4 = q0 + 4; q4 < q1 && ready; q4 += 4) {
+          int c[4];
+          V a[4][B2];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int q = q4 + u < q1 ? q4 + u : q1 - 1;
+            c[u] = ci[q];
+#pragma unroll
+            for (int e = 0; e < B2; ++e) a[u][e] = val[(size_t)B2 * q + e];
+          }
+          ready = ilu_group<V, BS>(a, c, q1 - q4, ow, s, &waitw);
+        }
+        // give up on this row after ILU_WAIT_TICKS, or once another row has (err), both
+        // read every 256 tries, or after max_tries tries
+        bool lost = false;
+        if (!ready) {
+          ++tries;
+          lost = tries >= max_tries ||
+                 ((tries & 255u) == 0 && (wall_clock64() - t_start > ILU_WAIT_TICKS ||
+                                          __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0));
+          if (lost) atomicOr(err, 1u);
+        }
+        if (ready || lost) {
+          U ww[BS * W];
+          if (lost) {
+#pragma unroll
+            for (int k = 0; k < BS * W; ++k) ww[k] = ILU_QNAN;
+          } else {
+            V o[BS];
+            if constexpr (UNIT) {
+#pragma unroll
+              for (int e = 0; e < BS; ++e) o[e] = s[e];
+            } else if constexpr (BS == 1) {
+              o[0] = s[0] / dg[0];
+            } else {
+#pragma unroll
+              for (int r = 0; r < BS; ++r) {
+                V acc = zero<V>();
+#pragma unroll
+                for (int k = 0; k < BS; ++k) acc = axpy(acc, dg[BS * r + k], s[k]);
+                o[r] = acc;
+              }
+            }
+            __builtin_memcpy(ww, o, sizeof(o));
+          }
+#pragma unroll
+          for (int k = 0; k < BS * W; ++k) ilu_st(ow + (size_t)BS * W * i + k, ww[k]);
+          pending = false;
+        }
+      }
+      if (__any(pending)) __builtin_amdgcn_s_sleep(8);
+    }
   }
 }
 
