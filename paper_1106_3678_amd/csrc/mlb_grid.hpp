@@ -536,15 +536,20 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
     }
     __syncthreads();
   };
-  // row `row` of the next product's input (every own row, before product())
+  // row `row` of the next product's input (every own row, before product()).  A value that
+  // holds the pending pattern (only from an x_0 that does) is a quiet NaN in both places.
   auto put = [&](int row, V v) {
+    U u[W];
+    __builtin_memcpy(u, &v, sizeof(V));
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      if (u[w] == Wd::pending) u[w] = Wd::qnan;
+    __builtin_memcpy(&v, u, sizeof(V));
     gl[row - lo] = v;
     if (P > 1) {
-      U u[W];
-      __builtin_memcpy(u, &v, sizeof(V));
       U* d = reinterpret_cast<U*>(xcur ? J.xb1 : J.xb) + (size_t)row * W;
 #pragma unroll
-      for (int w = 0; w < W; ++w) grid_st(d + w, u[w] == Wd::pending ? Wd::qnan : u[w]);
+      for (int w = 0; w < W; ++w) grid_st(d + w, u[w]);
     }
   };
   // after the reduction that follows a product: its exchange buffer is free again
