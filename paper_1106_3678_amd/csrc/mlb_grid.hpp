@@ -255,7 +255,26 @@ static_assert(grid_slots_fit<double>(4) && grid_slots_fit<double>(8) && grid_slo
               grid_slots_fit<double>(32) && grid_slots_fit<cplx<double>>(4) && grid_slots_fit<cplx<double>>(8) &&
               grid_slots_fit<cplx<double>>(16) && grid_slots_fit<cplx<double>>(32));
 
-// The recurrences of a step (scalar_program's, with the same arithmetic) as the
+// -a b, a / b (Smith's method) and |a|^2 with every fma written out: where the compiler chooses
+// which product of a complex expression it fuses, it chooses otherwise from variant to variant of
+// the kernel, and a system's result would depend on the largest n of its batch.
+__device__ inline double neg_mul(double a, double b) { return -(a * b); }
+__device__ inline cplx<double> neg_mul(cplx<double> a, cplx<double> b) {
+  return {fma(a.im, b.im, -(a.re * b.re)), fma(-a.re, b.im, -(a.im * b.re))};
+}
+__device__ inline double grid_div(double a, double b) { return a / b; }
+__device__ inline cplx<double> grid_div(cplx<double> a, cplx<double> b) {
+  if (fabs(b.re) >= fabs(b.im)) {
+    const double t = b.im / b.re, den = fma(b.im, t, b.re);
+    return {fma(a.im, t, a.re) / den, fma(-a.re, t, a.im) / den};
+  }
+  const double t = b.re / b.im, den = fma(b.re, t, b.im);
+  return {fma(a.re, t, a.im) / den, fma(a.im, t, -a.re) / den};
+}
+__device__ inline double grid_abs2(double a) { return a * a; }
+__device__ inline double grid_abs2(cplx<double> a) { return fma(a.re, a.re, a.im * a.im); }
+
+// The recurrences of a step (scalar_program's) as the
 // whole-solve kernel runs them: what they read of the state is loaded before the wait for
 // the sums, and the scalars (wave 0) and the triangular recurrence (wave 1) of a phase run
 // side by side.
@@ -289,35 +308,28 @@ struct GridPre {
     if (!tilde && phase != PH_COMBINE) return;
     const int lo = phase == PH_INNER ? i : 0, hi = phase == PH_COMBINE ? i : n;
     const Sc* d = tilde ? sums + 1 : sums;
-    if constexpr (!ROW) {
-      if (tilde) {
-        beta_tilde(&st, d, lo, n);
-      } else {
-        const Sc b = forward_subst(&st, d, 0, i);
-        const int s = threadIdx.x % WAVE;
-        if (s < i) st.beta[s] = b;
-      }
-    } else {
-      // forward_subst with the preloaded row
-      const int lane = threadIdx.x % WAVE, s = lo + lane;
-      const bool mine = s < hi;
-      Sc acc = mine ? d[lane] : zero<Sc>();
-      Sc xs = zero<Sc>();
+    const int lane = threadIdx.x % WAVE, s = lo + lane;
+    const bool mine = s < hi;
+    Sc acc = mine ? d[lane] : zero<Sc>();
+    Sc xs = zero<Sc>();
+    auto column = [&](int u, Sc ci, Sc su) {   // column lo + u of the triangle
+      const Sc xu = bcast_(neg_mul(acc, ci), u);
+      if (lane == u) xs = xu;
+      if (mine && lane > u) acc = axpy(acc, xu, su);
+    };
+    if constexpr (ROW) {   // the row preloaded
 #pragma unroll
       for (int u = 0; u < NB; ++u)
-        if (lo + u < hi) {
-          const Sc xu = bcast_(zero<Sc>() - acc * cinv, u);
-          if (lane == u) xs = xu;
-          if (mine && lane > u) acc = acc + xu * row[u];
-        }
-      if (mine) {
-        if (tilde) {
-          st.t[s] = xs;
-          st.tg[s] = zero<Sc>() - sc_div(xs, omega);
-        } else {
-          st.beta[s] = xs;
-        }
-      }
+        if (lo + u < hi) column(u, cinv, row[u]);
+    } else {
+      for (int u = 0; lo + u < hi; ++u) column(u, st.cinv[lo + u], mine ? st.S[s * NMAX + lo + u] : zero<Sc>());
+    }
+    if (!mine) return;
+    if (tilde) {
+      st.t[s] = xs;
+      st.tg[s] = zero<Sc>() - grid_div(xs, ROW ? omega : st.omega);
+    } else {
+      st.beta[s] = xs;
     }
   }
   // Every lane computes, lane 0 stores.
@@ -347,8 +359,8 @@ struct GridPre {
           finish(&st, -1);
         } else if (w0) {
           st.c[i] = ci;
-          st.cinv[i] = sc_div(from_real<Sc>(1.0), ci);
-          st.alpha = sc_div(e, ci);
+          st.cinv[i] = grid_div(from_real<Sc>(1.0), ci);
+          st.alpha = grid_div(e, ci);
         }
         break;
       }
@@ -376,7 +388,7 @@ struct GridPre {
         Sc om = rho / zz;
         if (st.kappa > 0) {
           const Sc rn = rho / (sqrt(zz) * sqrt(uu));
-          const double a = sqrt(abs2(rn));
+          const double a = sqrt(grid_abs2(rn));
           if (a < st.kappa && a != 0.0) om = (st.kappa / a) * om;
         }
         if (is_zero(om) || !finite(om)) {
@@ -572,7 +584,8 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
   // of global memory that nobody writes meanwhile (xg), or the vector put() before.
   // The first RB entries of the thread's first row of A stay in registers (held).
   constexpr int C = FMT == 0 ? 1 : 3;                                                        // columns of an entry
-  constexpr int RB = FMT == 0 ? (sizeof(V) * NB > 256 ? 4 : 8) : (sizeof(V) > 8 ? 2 : 4);   // entries in flight
+  constexpr int RT = FMT == 0 ? 8 : (sizeof(V) > 8 ? 2 : 4);                               // entries of a tree
+  constexpr int RB = FMT == 0 && sizeof(V) * NB > 256 ? RT / 2 : RT;                       // entries in flight
   auto entries = [&](const int* ci, const V* val, int beg, int end, int sub, int (&c)[RB], V (&v)[RB][C]) {
 #pragma unroll
     for (int k = 0; k < RB; ++k) {
@@ -623,7 +636,7 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
         beg = rp[br];
         end = rp[br + 1];
       }
-      V y = zero<V>();
+      V y = zero<V>(), part = zero<V>();
       int e0 = beg;
       do {
         int c[RB];
@@ -694,6 +707,18 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
         for (int m = 1; m < RB; m *= 2)
 #pragma unroll
           for (int k = 0; k < RB; k += 2 * m) add_(t[k], t[k + m]);
+        // a tree spans RT entries in every variant, so a row's sum does not depend on NB
+        if constexpr (RB < RT) {
+          if ((e0 - beg) % RT == 0 && e0 + RB < end) {
+            part = t[0];
+            e0 += RB;
+            continue;
+          }
+          if ((e0 - beg) % RT) {
+            add_(part, t[0]);
+            t[0] = part;
+          }
+        }
         add_(y, t[0]);
         e0 += RB;
       } while (e0 < end);
