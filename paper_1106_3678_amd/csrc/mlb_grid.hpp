@@ -429,7 +429,7 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
   unsigned* err = &J.st->ctl[GRID_ERR];
   int q_ring = 0;       // ring position of the next reduction
   int xcur = 0;         // exchange buffer of the next product
-  __shared__ V red[NW][NA];
+  __shared__ Sc red[NW][NA];
   __shared__ double tot[GB];
   V acc[NA];
   auto clear = [&] {
@@ -437,8 +437,9 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
     for (int d = 0; d < NA; ++d) acc[d] = zero<V>();
   };
 
-  // Sums over the group, in a fixed order (a tree over each wave, the waves of a workgroup
-  // in order, then the workgroups: every thread some of them, a tree over the lanes of a
+  // Sums over the group, in a fixed order (a thread's rows in V, from there on in Sc: the
+  // partial sums of fp32 values are fp64 beyond a thread's at most 8 rows; a tree over each
+  // wave, the waves of a workgroup in order, then the workgroups: every thread some of them, a tree over the lanes of a
   // wave that hold the same sum, the waves in order), and the recurrence of `phase` on
   // them: the scalars on wave 0, a triangular recurrence on wave 1.  The k-th sum is that
   // of acc[k] for k < base, of acc[k + shift] from base on.
@@ -452,9 +453,8 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
 #pragma unroll
     for (int d4 = 0; d4 < NA; d4 += 4)
       if (d4 + 4 > need0 && d4 < need1) {
-        const V z = zero<V>();
-        const V v = wave_sums4(acc[d4], d4 + 1 < NA ? acc[d4 + 1] : z, d4 + 2 < NA ? acc[d4 + 2] : z,
-                               d4 + 3 < NA ? acc[d4 + 3] : z, lane);
+        auto of = [&](int d) { return d < NA ? convert<Sc>(acc[d < NA ? d : 0]) : zero<Sc>(); };
+        const Sc v = wave_sums4(of(d4), of(d4 + 1), of(d4 + 2), of(d4 + 3), lane);
         if (lane >= WAVE - 4 && d4 + (lane & 3) < NA) red[wid][d4 + (lane & 3)] = v;
       }
     if (P > 1) grid_stores_done();
@@ -463,10 +463,9 @@ __device__ __forceinline__ void grid_solve(grid_job_ref<V, Sc> J, const int rank
     // word k of the workgroup's own sums
     auto own = [&](int k) {
       const int d = k / WS, src = d < base ? d : d + shift;
-      V v = red[0][src];
+      Sc s = red[0][src];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) add_(v, red[w][src]);
-      const Sc s = convert<Sc>(v);
+      for (int w = 1; w < NW; ++w) add_(s, red[w][src]);
       double t[WS];
       __builtin_memcpy(t, &s, sizeof(Sc));
       return WS == 2 && (k & 1) ? t[WS - 1] : t[0];
