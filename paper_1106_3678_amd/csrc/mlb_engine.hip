@@ -988,6 +988,7 @@ struct Engine {
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipMemcpyAsync(&o, dout, sizeof(o), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
+      if (o.lost) o.status = 2;
       if (o.status == 1) return true;
       if (o.status == 2) throw Error{MLB_EHIP, "a whole-solve launch gave up waiting for another workgroup"};
     }
@@ -2119,7 +2120,7 @@ static void batch_impl(mlb_solver* const* hs, int count, const void* const* b, v
     for (size_t q = 0; q < m; ++q) {
       const int k = todo[q];
       const GridOut& o = out[q];
-      if (o.status == 2) throw Error{MLB_EHIP, "a batched solve gave up waiting for another workgroup"};
+      if (o.status == 2 || o.lost) throw Error{MLB_EHIP, "a batched solve gave up waiting for another workgroup"};
       if (o.status == 0) {
         again.push_back(k);
         continue;

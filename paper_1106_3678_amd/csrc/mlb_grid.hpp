@@ -60,6 +60,7 @@ enum { GATE_CLOSED = 0, GATE_OPEN = 1, GATE_LEFT = 2 };
 // What the host reads after a solve.
 struct GridOut {
   int status;         // 0: the group left at its gate, 1: done, 2: a wait was lost
+  int lost;           // a workgroup lost a wait: after the last sums were out, too, when the first has its result
   int flag;
   long long iter;
   double err;
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(BLOCK) void k_grid_init(GridJob<V, Sc>* jobs, GridJ
     if (use_one) jobs[0] = one;
     for (int k = 0; k < 3; ++k) J.st->ctl[k] = 0;
     J.out->status = 0;
+    J.out->lost = 0;
     if (blockIdx.y == 0) *tick = 0;
   }
   if (J.P == 1) return;
@@ -1161,6 +1163,7 @@ __global__ __launch_bounds__(GB) void k_grid(const GridJob<V, Sc>* __restrict__ 
   }
   grid_solve<V, Sc, NB, FMT, KR>(J, rank, ss, sums, gl, zl, &lost, &setup_end);
   __syncthreads();
+  if (tid == 0 && lost) J.out->lost = 1;   // its rows of x may be missing, whatever the others have
   if (rank != 0) return;
   // the final state, without the ctl words and the Gram matrix
   unsigned long long* gw = reinterpret_cast<unsigned long long*>(J.st);
@@ -1168,15 +1171,14 @@ __global__ __launch_bounds__(GB) void k_grid(const GridJob<V, Sc>* __restrict__ 
   for (int w = tid; w < (int)(offsetof(State<Sc>, ctl) / 8); w += GB) gw[w] = lw[w];
   if (tid == 0) {
     // a lost wait is flagged before its workgroup publishes anything further
-    GridOut o;
-    o.status = lost || (J.P > 1 && grid_ld(&J.st->ctl[GRID_ERR])) ? 2 : 1;
-    o.flag = ss.done ? ss.flag : 1;
-    o.iter = ss.iter;
-    o.err = ss.err;
-    o.rr = re(ss.aux[0]);
-    o.bb = re(ss.aux[1]);
-    o.setup_ticks = setup_end - start;
-    *J.out = o;
+    GridOut* o = J.out;
+    o->status = lost || (J.P > 1 && grid_ld(&J.st->ctl[GRID_ERR])) ? 2 : 1;
+    o->flag = ss.done ? ss.flag : 1;
+    o->iter = ss.iter;
+    o->err = ss.err;
+    o->rr = re(ss.aux[0]);
+    o->bb = re(ss.aux[1]);
+    o->setup_ticks = setup_end - start;
   }
 }
 
