@@ -2073,9 +2073,23 @@ static void batch_impl(mlb_solver* const* hs, int count, const void* const* b, v
   } ev;
   HIP_TRY(hipEventCreate(&ev.t0));
   HIP_TRY(hipEventCreate(&ev.t1));
-  // a system whose group left at its gate is started again
-  for (int start = 0; !todo.empty(); ++start) {
-    if (start == GRID_STARTS) throw Error{MLB_EHIP, "a batched system's workgroups were never all running"};
+  // A system whose group left at its gate is started again: of a batch that does not fit the
+  // card at once, with solves that take longer than a group waits, every start finishes some.
+  // After GRID_STARTS starts in a row that finished none the launches solve the others.
+  for (int idle = 0; !todo.empty();) {
+    if (idle == GRID_STARTS) {
+      for (int k : todo) {
+        Engine<V64>& e = impl_of(hs[k])->e64;
+        struct Launches {   // also when the solve throws
+          bool& solo;
+          const bool was;
+          ~Launches() { solo = was; }
+        } launches{e.grid_solo, e.grid_solo};
+        e.grid_solo = false;
+        solve_solver(hs[k], b[k], x[k], Q[k], ldq[k], res ? res + k : nullptr);
+      }
+      return;
+    }
     const size_t m = todo.size();
     size_t wgs = 0;
     int waiting = 0;   // workgroups that wait for others
@@ -2138,6 +2152,7 @@ static void batch_impl(mlb_solver* const* hs, int count, const void* const* b, v
       e.ldq = ldq[k];
       hs[k]->solved = true;
     }
+    idle = again.size() == m ? idle + 1 : 0;
     todo.swap(again);
   }
 }
