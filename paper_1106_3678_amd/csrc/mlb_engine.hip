@@ -35,6 +35,7 @@
 #include "../../include/mlbicgstab.h"
 #include "mlb_kernels.hpp"
 #include "mlb_spmv.hpp"
+#include "mlb_gate.hpp"
 #include "mlb_grid.hpp"
 #include "mlb_precond.hpp"
 #include "mlb_ilu.hpp"
@@ -751,38 +752,23 @@ __global__ void k_init_state(State<Sc>* st, double tol, long long maxit, double 
 
 // ------------------------------------------------------------------ whole-solve launches
 
-// The workgroups of a whole-solve launch (mlb_grid.hpp) wait for each other, so
-// launches of one process share the device's workgroup slots through this gate: a
-// launch takes its share before it starts, and two of them never hold the device half
-// each, waiting.  (Other launches end by themselves; a group of another process that
+// Holds a share of the current device's workgroup slots for a whole-solve launch
+// (mlb_gate.hpp).  (Other launches end by themselves; a group of another process that
 // holds slots makes the kernel leave at its own gate, and it is started again.)
 struct GridGate {
   static constexpr int MAX_DEVICES = 64;
-  struct Dev {
-    std::mutex mu;
-    std::condition_variable cv;
-    double used = 0;
-  };
-  static Dev& dev() {
-    static Dev devs[MAX_DEVICES];
+  static ShareGate& dev() {
+    static ShareGate devs[MAX_DEVICES];
     int d = 0;
     (void)hipGetDevice(&d);
     return devs[d >= 0 && d < MAX_DEVICES ? d : 0];
   }
-  Dev& d;
-  double share;
-  explicit GridGate(double s) : d(dev()), share(std::min(s, 1.0)) {
-    std::unique_lock<std::mutex> lk(d.mu);
-    d.cv.wait(lk, [&] { return d.used + share <= 1.0 + 1e-9; });
-    d.used += share;
-  }
-  ~GridGate() {
-    {
-      std::lock_guard<std::mutex> lk(d.mu);
-      d.used -= share;
-    }
-    d.cv.notify_all();
-  }
+  ShareGate& d;
+  const double share;
+  explicit GridGate(double s) : d(dev()), share(std::min(s, 1.0)) { d.enter(share); }
+  ~GridGate() { d.leave(share); }
+  GridGate(const GridGate&) = delete;
+  GridGate& operator=(const GridGate&) = delete;
 };
 constexpr int GRID_STARTS = 20;   // starts of a launch whose groups left at their gate
 
