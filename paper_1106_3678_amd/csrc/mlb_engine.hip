@@ -765,7 +765,12 @@ struct GridGate {
   }
   ShareGate& d;
   const double share;
-  explicit GridGate(double s) : d(dev()), share(std::min(s, 1.0)) { d.enter(share); }
+  // The share covers the launch itself, not what the stream still holds before it: other
+  // threads' launches would wait for that, too.  (Up to an eighth of the device it may.)
+  GridGate(double want, hipStream_t s) : d(dev()), share(std::min(want, 1.0)) {
+    if (share > 0.125) HIP_TRY(hipStreamSynchronize(s));
+    d.enter(share);
+  }
   ~GridGate() { d.leave(share); }
   GridGate(const GridGate&) = delete;
   GridGate& operator=(const GridGate&) = delete;
@@ -969,7 +974,7 @@ struct Engine {
     auto* dj = reinterpret_cast<GridJob<V, Sc>*>(reinterpret_cast<char*>(part2) + 256);
     static_assert(256 + sizeof(GridJob<V, Sc>) <= PSUM_GRID * (NMAX + 1) * sizeof(double), "job fits part2");
     for (int t = 0; t < GRID_STARTS; ++t) {
-      GridGate gate(grid_P > 1 ? (double)grid_P / grid_cap : 0.0);
+      GridGate gate(grid_P > 1 ? (double)grid_P / grid_cap : 0.0, s);
       grid_launch<V>(dj, nullptr, &J, 1, grid_P, nb, A.format == MLB_BSR3, grid_kr(), &st->ctl[3], s);
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipMemcpyAsync(&o, dout, sizeof(o), hipMemcpyDeviceToHost, s));
@@ -2106,7 +2111,7 @@ static void batch_impl(mlb_solver* const* hs, int count, const void* const* b, v
     HIP_TRY(hipMemcpyAsync(buf, host.data(), bytes, hipMemcpyHostToDevice, s));
     std::vector<GridOut> out(m);
     {
-      GridGate gate((double)waiting / cap);
+      GridGate gate((double)waiting / cap, s);
       HIP_TRY(hipEventRecord(ev.t0, s));
       grid_launch<V64>(dj, dmap, nullptr, (int)m, (int)wgs, nb, 0, kr, tick, s);
       HIP_TRY(hipGetLastError());
