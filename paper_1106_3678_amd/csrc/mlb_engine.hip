@@ -302,6 +302,7 @@ static IluLds ilu_lds(int bs, int words, int w) {
   const size_t slot = (size_t)ilu_slot_words(bs, words, w) * 8, place = (size_t)bs * words * 8;
   const size_t room = (size_t)lds - 1024;
   IluLds r;
+  r.room = (int)room;
   r.ring = bs == 1 ? 8192 : 1024;
   while (r.ring > 512 && r.ring * place > room / 2) r.ring /= 2;
   r.slots = (int)std::min<size_t>(bs == 1 ? 16 : 8, (room - r.ring * place) / slot);
@@ -417,13 +418,14 @@ static void ilu_solve1(const IluFactor<V>& f, const Mat<V>& M, const IluRows<V>&
       M.ci, M.val, rows, f.nbrows, f.block, f.lds, in, xch, out, next, f.ctl + which, f.ctl + 2, f.max_tries, done);
 }
 
-// Lets the four kernels of one factor take the LDS a block needs.
+// Lets the four kernels of a kind of factor take all the LDS there is: the limit belongs to
+// the kernel, and other solvers' launches may ask for more than this one's.
 template <class V, int BS>
 static void ilu_allow_lds(int lds) {
-  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-  HIP_TRY(hipFuncSetAttribute((const void*)k_ilu_solve_block<V, BS, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  const void* kernels[] = {(const void*)k_ilu_solve_block<V, BS, true, true>, (const void*)k_ilu_solve_block<V, BS, true, false>,
+                           (const void*)k_ilu_solve_block<V, BS, false, true>,
+                           (const void*)k_ilu_solve_block<V, BS, false, false>};
+  for (const void* k : kernels) HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
 }
 
 // Marks f.tmid pending and resets both claim counters: the start of a pair of one-launch solves.
@@ -553,8 +555,8 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   const int w = ilu_width(A.nnz, m);
   f.block = ilu_block_rows(m);
   f.lds = ilu_lds(bs, (int)sizeof(V) / 8, w);
-  if (bs == 1) ilu_allow_lds<V, 1>((int)f.lds.bytes);
-  else ilu_allow_lds<V, 3>((int)f.lds.bytes);
+  if (bs == 1) ilu_allow_lds<V, 1>(f.lds.room);
+  else ilu_allow_lds<V, 3>(f.lds.room);
   // the solve orders of a matrix's lower and upper solves (index arrays on the host), side by
   // side: each is one long scan of the pattern
   auto orders = [&](const std::vector<int>& mrp, const std::vector<int>& mci, IluOrder& lo, IluOrder& up) {

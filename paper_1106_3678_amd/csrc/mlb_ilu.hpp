@@ -231,6 +231,7 @@ struct IluLds {
   int slots = 0;
   int safe = 0;    // largest distance of a value read from the ring
   size_t bytes = 0;
+  int room = 0;    // bytes that a workgroup may have
 };
 // 64-bit words of a slot for entries of b2 values of `words` words: the row's partial
 // sums, its w entries, its diagonal (scalars: and the reciprocal), then w + 2 ints a lane.
