@@ -323,7 +323,7 @@ static int level_grid(int count) { return std::max(1, std::min((count + BLOCK - 
 
 // The stored entries [q0, q1) left (lower) or right of row i's diagonal (every row has one,
 // checked before), as {i, q0, q1, 0}.
-static int4 ilu_row(const std::vector<int>& rp, const std::vector<int>& ci, int i, bool lower) {
+__attribute__((always_inline)) static inline int4 ilu_row(const int* rp, const int* ci, int i, bool lower) {
   int qd = rp[i];
   for (int q = rp[i]; q < rp[i + 1]; ++q)
     if (ci[q] == i) {
@@ -334,10 +334,11 @@ static int4 ilu_row(const std::vector<int>& rp, const std::vector<int>& ci, int 
 }
 
 // The order of one triangular solve (host).  lv: the rows in solve order: by block, first from
-// the first row (lower) or the last, and by level inside a block.  Over every ILU_SAMPLE-th row
-// (by level), rows: how many, side: their entries, far: those that a block reads from memory,
-// loose: those beyond the w packed ones.
-constexpr int ILU_SAMPLE = 4;
+// the first row (lower) or the last, and by level inside a block.  Over some blocks, evenly
+// spread (up to 2 ILU_SAMPLE; all would take a seventh of the time of an order), rows: their
+// rows, side: the rows' entries, far: those that a block reads from memory, loose: those beyond
+// the w packed ones.
+constexpr size_t ILU_SAMPLE = 4;
 struct IluOrder {
   std::vector<int> ord, ptr, cstart, bchunk;   // rows by level, level pointers, chunks (see IluRows)
   std::vector<int4> lv;
@@ -349,35 +350,41 @@ static IluOrder ilu_order(const std::vector<int>& rp, const std::vector<int>& ci
   IluOrder o;
   level_sets(rp, ci, lower, o.ord, o.ptr);
   const size_t m = o.ord.size();
-  std::vector<int> lev(m), pos(m);   // level of every position, position of every row
-  size_t level = 0;
+  std::vector<int> lev(m);   // level of every position
   o.lv.resize(m);
   std::vector<int> fill((m + block - 1) / block);
   for (size_t k = 0; k < fill.size(); ++k) fill[k] = (int)(k * block);
-  for (size_t r = 0; r < m; ++r) {
-    const int i = o.ord[r];
-    while ((int)r >= o.ptr[level + 1]) ++level;
-    const size_t k = (lower ? (size_t)i : m - 1 - i) / block;
-    const int t = fill[k]++;
-    lev[t] = (int)level;
-    pos[i] = t;
-    const int4 row = o.lv[t] = ilu_row(rp, ci, i, lower);
-    if (r % ILU_SAMPLE) continue;
-    ++o.rows;
-    o.side += row.z - row.y;
-    o.loose += std::max(0, row.z - row.y - w);
-    for (int q = row.y; q < row.z; ++q) {   // its row is of an earlier level
-      const int tj = pos[ci[q]];
-      o.far += tj < (int)(k * block) || t - tj > safe;
+  {
+    const int *rpp = rp.data(), *cip = ci.data(), *ord = o.ord.data();
+    int *levp = lev.data(), *fillp = fill.data();
+    int4* lv = o.lv.data();
+    for (size_t level = 0; level + 1 < o.ptr.size(); ++level)
+      for (int r = o.ptr[level], end = o.ptr[level + 1]; r < end; ++r) {
+        const int i = ord[r], t = fillp[(unsigned)(lower ? i : (int)m - 1 - i) / (unsigned)block]++;
+        levp[t] = (int)level;
+        lv[t] = ilu_row(rpp, cip, i, lower);
+      }
+  }
+  std::vector<int> pos(block);   // of the rows of one block, in it
+  const size_t step = std::max<size_t>(1, fill.size() / ILU_SAMPLE);
+  for (size_t k = step / 2; k < fill.size(); k += step) {
+    const int b0 = (int)(k * block), n = std::min(block, (int)m - b0);
+    auto place = [&](int i) { return (lower ? i : (int)m - 1 - i) - b0; };   // < 0: in an earlier block
+    for (int t = 0; t < n; ++t) pos[place(o.lv[b0 + t].x)] = t;
+    o.rows += n;
+    for (int t = 0; t < n; ++t) {
+      const int4 row = o.lv[b0 + t];
+      o.side += row.z - row.y;
+      o.loose += std::max(0, row.z - row.y - w);
+      for (int q = row.y; q < row.z; ++q) o.far += place(ci[q]) < 0 || t - pos[place(ci[q])] > safe;
     }
   }
   // chunks: at most 64 positions of one level of one block
-  o.bchunk.assign(1, 0);
-  for (size_t t = 0; t < m; ++t)
-    if (t % block == 0 || lev[t] != lev[t - 1] || (int)t - o.cstart.back() == WAVE) {
-      if (t && t % block == 0) o.bchunk.push_back((int)o.cstart.size());
-      o.cstart.push_back((int)t);
-    }
+  for (int b0 = 0; b0 < (int)m; b0 += block) {
+    o.bchunk.push_back((int)o.cstart.size());
+    for (int t = b0, end = std::min((int)m, b0 + block); t < end; ++t)
+      if (t == b0 || lev[t] != lev[t - 1] || t - o.cstart.back() == WAVE) o.cstart.push_back(t);
+  }
   o.bchunk.push_back((int)o.cstart.size());
   o.cstart.push_back((int)m);
   return o;
@@ -567,7 +574,7 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   auto by_level = [&](IluRows<V>& r, const IluOrder& o, const std::vector<int>& mrp, const std::vector<int>& mci,
                       bool lower) {
     std::vector<int4> lv(m);
-    for (int t = 0; t < m; ++t) lv[t] = ilu_row(mrp, mci, o.ord[t], lower);
+    for (int t = 0; t < m; ++t) lv[t] = ilu_row(mrp.data(), mci.data(), o.ord[t], lower);
     r.lv = al.get<int4>(m);
     HIP_TRY(hipMemcpyAsync(r.lv, lv.data(), sizeof(int4) * m, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));   // lv is copied before it goes
