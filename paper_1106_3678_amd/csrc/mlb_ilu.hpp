@@ -585,7 +585,8 @@ __global__ __launch_bounds__((ilu_threads<BS>())) void k_ilu_solve_block(
     for (int u = 0; u < ILU_W; ++u)
       if (u < w_) {
 #pragma unroll
-        for (int e = 0; e < B2; ++e) put(f + (f_a + (u * B2 + e) * W) * WAVE, a[u][e]);
+        for (int e = 0; e < B2; ++e)   // one subtracted here is not in the row's rest (an infinite one times 0 would be)
+          put(f + (f_a + (u * B2 + e) * W) * WAVE, BS == 1 && c[u] >= 0 ? zero<V>() : a[u][e]);
         fi[u * WAVE + lane] = c[u] < -1 ? ((-2 - c[u] - b0) & mask_ring) * (BS * W) : -1;
       }
     if constexpr (!UNIT) {
