@@ -381,7 +381,7 @@ typedef struct mlb_server* mlb_server_handle;
 
 typedef struct {
   uint64_t budget_bytes;    /* HBM admission budget for the requests' footprints */
-  int32_t max_inflight;     /* workers = multi-launch solves in flight, 1..64  */
+  int32_t max_inflight;     /* workers = solves in flight beside batches, 1..64 */
   int32_t small_n_max;      /* CSR fp64 requests without preconditioner and with
                                at most this many rows go to the batchers
                                (0: MLB_SERVER_SMALL_N, -1: none)              */

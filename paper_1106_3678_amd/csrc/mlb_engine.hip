@@ -9,10 +9,10 @@
 // real or complex).  Every step of the iteration is a kernel from
 // mlb_kernels.hpp; the host only enqueues them, cycle by cycle, and watches a
 // host-mapped "done" flag the device raises when the solve ends.  The host
-// (Systems of up to some hundred thousand rows run whole in one launch instead,
-// mlb_grid.hpp.)  It stays at most two cycles ahead of the device, so the iteration never waits
+// stays at most two cycles ahead of the device, so the iteration never waits
 // for the host and the kernels of at most one cycle run after the end (they
-// return at once because the device flag is set).
+// return at once because the device flag is set).  Systems of up to some hundred
+// thousand rows run whole in one launch instead (mlb_grid.hpp, Engine::pick_grid).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -921,9 +921,10 @@ struct Engine {
   // (a row's times rows a lane) 40: 104 / 87 (130,000 rows), 46: 112 / 97 (500,000), 48: 98 / 104
   // (260,000), 62: 131 / 137 (500,000); complex 24: 91 / 85 (260,000), 32: 101 / 107, 35: 140 /
   // 139 (500,000), 46: 162 / 175; fp32 62: 154 / 127 (500,000), 80: 173 / 217 (260,000), 93: 198 /
-  // 213, but 8 rows of 12 217 / 194 (1,000,000); 3x3 blocks 20: 61 / 57 (258,000), 28: 74 / 83 (510,000).  One long row among
-  // 100,000 of five: 96 entries 39 / 33, 192 44 / 49, 1,024 87 / 184.  A long row of A^H
-  // is walked n - 1 times a solve.
+  // 213, but 8 rows of 12 217 / 194 (1,000,000); 3x3 blocks 20: 61 / 57 (258,000), 28: 74 / 83
+  // (510,000).  One long row among 100,000 of five: 96 entries 39 / 33, 192 44 / 49, 1,024 87 /
+  // 184.  A long row of A^H is walked n - 1 times a solve: 40 iterations at 100,000 rows with
+  // one of 1,300 entries 42 / 30 each, 2,000 44 / 36.
   bool rows_suit_grid() const {
     const bool blocks = A.format == MLB_BSR3;
     const double row = (double)A.nnz / A.nbrows, walk = row * std::max(1.0, (double)grid_R / GB);
@@ -2799,7 +2800,7 @@ static void batcher_main(Server* S) {
       for (auto& h : hs) h.reset();
       (void)hipStreamSynchronize(st);
       // a request with restarts whose batched run converged with its true residual not below
-      // tol goes on from its x on the multi-launch iteration, within its admitted footprint
+      // tol goes on from its x in a solve of its own, within its admitted footprint
       for (size_t k = 0; k < batch.size(); ++k) {
         Request& r = *batch[k];
         if (r.rc != 0 || r.opt.max_restarts <= 0 || !(r.res.err_true >= r.opt.tol) || r.res.iter >= r.opt.maxit)

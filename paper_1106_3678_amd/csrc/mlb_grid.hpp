@@ -23,10 +23,11 @@
 // latency of a reduction or an exchange.
 // Words are marked pending again once everybody has read them:
 //  * slots: phase q uses ring position q mod 4.  A workgroup all of whose waves
-//    have read their sums of phase q + 1 knows that everybody has finished reading phase q (they
-//    published q + 1 afterwards) and marks its words of phase q; it waits for
-//    its outstanding stores before it publishes phase q + 2, so a reader that
-//    has passed q + 3 finds them pending, or the new ones of q + 4.
+//    have read their sums of phase q + 1 knows that everybody has finished
+//    reading phase q (they published q + 1 afterwards) and marks its words of
+//    phase q; it waits for its outstanding stores before it publishes phase
+//    q + 2, so a reader that has passed q + 3 finds them pending, or the new
+//    ones of q + 4.
 //  * exchange buffers alternate: the rows of exchange e are marked once the
 //    reduction after its product has been read, and used again by e + 2.
 // The workgroups of a group must all be running.  Logical workgroup numbers are
@@ -151,7 +152,7 @@ __device__ inline void grid_st(U* p, U v) {
 // Waits until this wave's stores have reached memory.
 __device__ inline void grid_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Sum over the 64 lanes with DPP moves (VALU only, a fixed order), in lane 63.
+// A DPP move (VALU only): lanes without a source get 0.
 template <int CTRL>
 __device__ inline float dpp0_(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
@@ -166,17 +167,6 @@ template <int CTRL, class R>
 __device__ inline cplx<R> dpp0_(cplx<R> v) {
   return {dpp0_<CTRL>(v.re), dpp0_<CTRL>(v.im)};
 }
-template <class T>
-__device__ inline T wave_sum63(T v) {
-  add_(v, dpp0_<0x111>(v));   // row_shr:1
-  add_(v, dpp0_<0x112>(v));   // row_shr:2
-  add_(v, dpp0_<0x114>(v));   // row_shr:4
-  add_(v, dpp0_<0x118>(v));   // row_shr:8
-  add_(v, dpp0_<0x142>(v));   // row_bcast:15
-  add_(v, dpp0_<0x143>(v));   // row_bcast:31
-  return v;
-}
-
 // Sums of four values over the 64 lanes: lane k (and every lane equal to it mod 4) of
 // the upper half of each row of 16 ends with the sum of v[k % 4].  Halving: two exchange
 // steps leave each lane one of the four, so 7 steps of moves and adds do for 24.
