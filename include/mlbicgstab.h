@@ -207,7 +207,11 @@ typedef struct {
  */
 int mlbicgstab_create(const mlb_matrix* A, const mlb_options* opt, void* hip_stream, mlb_handle* out);
 
-/* Bytes of device memory create() would allocate for A and opt. */
+/*
+ * Bytes of device memory create() would allocate for A and opt, at most: an
+ * ILU(0) whose triangular solves go level by level takes less, and where memory
+ * (or a server's budget) holds only that, they do.
+ */
 int mlbicgstab_workspace_size(const mlb_matrix* A, const mlb_options* opt, size_t* bytes);
 
 /*

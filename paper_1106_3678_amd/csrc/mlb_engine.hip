@@ -516,8 +516,9 @@ static std::vector<int> to_host(const int* d, size_t count, hipStream_t s) {
 // pattern checks, the level sets, the factorisation level by level, the
 // conjugate transpose with its diagonal inverses.  Throws MLB_EINVAL for a
 // missing diagonal, a repeated column in a row or a zero / singular pivot.
+// lean: both pairs of solves by level, which takes less memory than rows packed for blocks.
 template <class V>
-static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t s) {
+static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t s, bool lean) {
   const int m = A.nbrows;
   const int bs = A.format == MLB_BSR3 ? 3 : 1;
   const int b2 = bs * bs;
@@ -537,7 +538,7 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   f.dpos = al.get<int>(m);
   f.dinv = al.get<V>((size_t)m * b2);
   f.tmid = al.get<V>((size_t)m * bs);
-  f.tend = al.get<V>((size_t)m * bs);
+  if (!lean) f.tend = al.get<V>((size_t)m * bs);
   f.ctl = al.get<unsigned>(4);
   k_fill<unsigned><<<1, BLOCK, 0, s>>>(f.ctl, 4, 0u);
   // a test hook: a positive MLB_ILU_MAX_TRIES makes every row that waits that many tries give up
@@ -601,7 +602,7 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   };
   IluOrder lo, up;
   orders(hrp, hci, lo, up);
-  f.blocksF = ilu_by_blocks(lo, up);
+  f.blocksF = !lean && ilu_by_blocks(lo, up);
   if (f.blocksF) {
     rows(f.rowsL, lo, false);
     rows(f.rowsU, up, true);
@@ -637,7 +638,7 @@ static void build_ilu(const Mat<V>& A, IluFactor<V>& f, Allocs& al, hipStream_t 
   const std::vector<int> hrpH = to_host(f.FH.rp, (size_t)m + 1, s);
   const std::vector<int> hciH = to_host(f.FH.ci, (size_t)A.nnz, s);
   orders(hrpH, hciH, lo, up);   // lo.ord was copied before the synchronisation above
-  f.blocksH = ilu_by_blocks(lo, up);
+  f.blocksH = !lean && ilu_by_blocks(lo, up);
   if (f.blocksH) {
     rows(f.rowsHf, lo, true);
     rows(f.rowsHb, up, false);
@@ -663,12 +664,13 @@ static int ilu_width(long long nnz, int m) {
   return (int)std::max<long long>(1, std::min<long long>(ILU_W, (nnz - m + 2LL * m - 1) / (2LL * m)));
 }
 
-// Device bytes build_ilu allocates (beside the transpose's own temporaries).
-static size_t ilu_bytes(long long nnz, int m, int bs, size_t sv) {
+// Device bytes build_ilu allocates (beside the transpose's own temporaries), at most.
+static size_t ilu_bytes(long long nnz, int m, int bs, size_t sv, bool lean) {
   const size_t b2 = (size_t)bs * bs;
-  return (size_t)nnz * 4 * 2 + (size_t)nnz * b2 * sv * 2 + (size_t)(m + 1) * 4 + (size_t)m * 4 * 3 +
-         (size_t)m * (sizeof(int4) + 12 + ilu_width(nnz, m) * (4 + b2 * sv)) * 4 + (size_t)m * b2 * sv * 4 +
-         (size_t)m * bs * sv * 2 + 16;
+  const size_t level = (size_t)nnz * 4 * 2 + (size_t)nnz * b2 * sv * 2 + (size_t)(m + 1) * 4 + (size_t)m * 4 * 3 +
+                       (size_t)m * sizeof(int4) * 4 + (size_t)m * b2 * sv * 2 + (size_t)m * bs * sv + 16;
+  if (lean) return level;
+  return level + (size_t)m * (12 + ilu_width(nnz, m) * (4 + b2 * sv)) * 4 + (size_t)m * b2 * sv * 2 + (size_t)m * bs * sv;
 }
 
 // ------------------------------------------------------------------ launch dispatch
@@ -1485,6 +1487,7 @@ struct mlb_solver {
   bool noalloc = false;       // everything in the caller's arena, no host-mapped flags or events
   int n_active = 0;           // shadow vectors of the next solve (<= opt.n, the workspace's)
   int longest = 0;            // entries of A's longest (block) row
+  bool lean_ilu = false;      // ILU(0) in less memory (build_ilu)
   Allocs al;
   std::unique_ptr<Impl<double, float>> real;
   std::unique_ptr<Impl<cplx<double>, cplx<float>>> cpx;
@@ -1597,7 +1600,7 @@ static void create_impl(mlb_solver* h, const mlb_matrix* Adesc, Impl<V64, V32>& 
   }
   if (h->opt.precond == MLB_PRECOND_ILU0) {
     // M = ILU(0) of A; the iteration multiplies by A after M^{-1}
-    build_ilu(A, im.ilu, h->al, h->s);
+    build_ilu(A, im.ilu, h->al, h->s, h->lean_ilu);
     im.has_ilu = true;
     im.e64.ilu = &im.ilu;
   }
@@ -1927,12 +1930,12 @@ static int guarded(F&& f) {
 // flags: two pinned host-mapped ints for the engines' done flags, or NULL.
 // arena / arena_cap: allocation-free mode, every device buffer carved from the
 // caller's region (see Allocs).
-static std::unique_ptr<mlb_solver> create_solver(const mlb_matrix* A, const mlb_options* opt, hipStream_t stream,
-                                                 bool ordered, int* flags, char* arena = nullptr,
-                                                 size_t arena_cap = 0) {
+static std::unique_ptr<mlb_solver> create_once(const mlb_matrix* A, const mlb_options* opt, hipStream_t stream,
+                                               bool ordered, int* flags, char* arena, size_t arena_cap, bool lean) {
   check_matrix(A);
   check_options(opt);
   auto h = std::make_unique<mlb_solver>();
+  h->lean_ilu = lean;
   h->dtype = A->dtype;
   h->format = A->format;
   h->N = (int)A->nrows;
@@ -1979,6 +1982,18 @@ static std::unique_ptr<mlb_solver> create_solver(const mlb_matrix* A, const mlb_
     create_impl(h.get(), A, *h->cpx);
   }
   return h;
+}
+
+// As create_once; an ILU(0) solver that does not fit the memory left is built with solves by level.
+static std::unique_ptr<mlb_solver> create_solver(const mlb_matrix* A, const mlb_options* opt, hipStream_t stream,
+                                                 bool ordered, int* flags, char* arena = nullptr,
+                                                 size_t arena_cap = 0, bool lean = false) {
+  try {
+    return create_once(A, opt, stream, ordered, flags, arena, arena_cap, lean);
+  } catch (const Error& e) {
+    if (e.code != MLB_ENOMEM || opt->precond != MLB_PRECOND_ILU0 || lean) throw;
+  }
+  return create_once(A, opt, stream, ordered, flags, arena, arena_cap, true);
 }
 
 // Number of shadow vectors of the following solves (1 <= n <= the n of create).
@@ -2181,6 +2196,29 @@ static int solve_batch(mlb_solver* const* hs, int count, const void* const* b, v
   return 0;
 }
 
+// Device bytes create_solver allocates for A and opt, at most.
+static size_t workspace_bytes(const mlb_matrix* A, const mlb_options* opt, bool lean) {
+  const int N = (int)A->nrows;
+  const int nbr = A->format == MLB_BSR3 ? N / 3 : N;
+  const int bs = A->format == MLB_BSR3 ? 9 : 1;
+  const bool c = A->dtype == MLB_C128;
+  const size_t sv = c ? 16 : 8;
+  const bool tf = opt->transpose_free != 0;
+  size_t t = tf ? 0 : (size_t)(nbr + 1) * 4 + (size_t)A->nnz * 4 + (size_t)A->nnz * bs * sv;   // A^H
+  t += c ? Engine<cplx<double>>::bytes(N, opt->n, tf) : Engine<double>::bytes(N, opt->n, tf);
+  t += (size_t)N * sv;                                                                   // r64
+  if (opt->precond == MLB_PRECOND_JACOBI)                                                // M, M^{-1}, A M^{-1}
+    t += (size_t)nbr * bs * 2 * sv + (size_t)A->nnz * bs * sv;
+  if (opt->precond == MLB_PRECOND_ILU0)                                                  // factor, its transpose, M^{-1} v
+    t += ilu_bytes(A->nnz, nbr, A->format == MLB_BSR3 ? 3 : 1, sv, lean) + (size_t)N * sv;
+  if (opt->precision == MLB_PREC_FP32_IR) {
+    t += (size_t)A->nnz * bs * (tf ? sv / 2 : sv);                                       // fp32 A (and A^H) values
+    t += c ? Engine<cplx<float>>::bytes(N, opt->n, tf) : Engine<float>::bytes(N, opt->n, tf);
+    t += (size_t)N * (2 + opt->n) * (sv / 2);
+  }
+  return t;
+}
+
 }  // namespace mlb
 
 // ------------------------------------------------------------------ C ABI
@@ -2192,25 +2230,7 @@ int mlbicgstab_workspace_size(const mlb_matrix* A, const mlb_options* opt, size_
     check_matrix(A);
     check_options(opt);
     if (!bytes) throw Error{MLB_EINVAL, "bytes pointer is NULL"};
-    const int N = (int)A->nrows;
-    const int nbr = A->format == MLB_BSR3 ? N / 3 : N;
-    const int bs = A->format == MLB_BSR3 ? 9 : 1;
-    const bool c = A->dtype == MLB_C128;
-    const size_t sv = c ? 16 : 8;
-    const bool tf = opt->transpose_free != 0;
-    size_t t = tf ? 0 : (size_t)(nbr + 1) * 4 + (size_t)A->nnz * 4 + (size_t)A->nnz * bs * sv;   // A^H
-    t += c ? Engine<cplx<double>>::bytes(N, opt->n, tf) : Engine<double>::bytes(N, opt->n, tf);
-    t += (size_t)N * sv;                                                                   // r64
-    if (opt->precond == MLB_PRECOND_JACOBI)                                                // M, M^{-1}, A M^{-1}
-      t += (size_t)nbr * bs * 2 * sv + (size_t)A->nnz * bs * sv;
-    if (opt->precond == MLB_PRECOND_ILU0)                                                  // factor, its transpose, M^{-1} v
-      t += ilu_bytes(A->nnz, nbr, A->format == MLB_BSR3 ? 3 : 1, sv) + (size_t)N * sv;
-    if (opt->precision == MLB_PREC_FP32_IR) {
-      t += (size_t)A->nnz * bs * (tf ? sv / 2 : sv);                                       // fp32 A (and A^H) values
-      t += c ? Engine<cplx<float>>::bytes(N, opt->n, tf) : Engine<float>::bytes(N, opt->n, tf);
-      t += (size_t)N * (2 + opt->n) * (sv / 2);
-    }
-    *bytes = t;
+    *bytes = workspace_bytes(A, opt, false);
     return 0;
   });
 }
@@ -2465,6 +2485,7 @@ struct Request {
   const void* Q = nullptr;
   int64_t ldq = 0;
   size_t footprint = 0;
+  bool lean = false;               // its ILU(0) in less memory, so that it fits the budget
   double t_submit = 0, t_start = 0, t_done = 0;
   mlb_result res{};
   int rc = 0;
@@ -2488,6 +2509,7 @@ struct SeqEntry {
   double t_prev = -1.0;
   std::unique_ptr<mlb_solver> h;
   size_t footprint = 0;
+  bool lean = false;       // as in Request
   bool admitted = false;   // footprint counted in the server's used bytes
   bool busy = false;       // a worker is running one of its requests
   bool ending = false;     // mlb_server_end_sequence was called
@@ -2517,7 +2539,7 @@ struct Server {
 
 static void run_request(Request& r, hipStream_t st, int* flags) {
   try {
-    auto h = create_solver(&r.A, &r.opt, st, true, flags);
+    auto h = create_solver(&r.A, &r.opt, st, true, flags, nullptr, 0, r.lean);
     r.rc = solve_solver(h.get(), r.b, r.x, r.Q, r.ldq, &r.res);
     HIP_TRY(hipStreamSynchronize(st));
     h.reset();
@@ -2539,7 +2561,7 @@ static void run_seq_request(SeqEntry& q, Request& r, hipStream_t st) {
     if (!q.h) {
       mlb_options o = q.opt;
       o.n = q.n_max;
-      q.h = create_solver(&q.A, &o, st, true, nullptr);
+      q.h = create_solver(&q.A, &o, st, true, nullptr, nullptr, 0, q.lean);
     }
     set_stream(q.h.get(), st);
     set_active_n(q.h.get(), q.n_next);
@@ -2557,6 +2579,14 @@ static void run_seq_request(SeqEntry& q, Request& r, hipStream_t st) {
     r.rc = MLB_EHIP;
     r.err = e.what();
   }
+}
+
+// What a request takes of the server's budget; lean: an ILU(0) that exceeds the whole budget
+// in its usual form, but not with solves by level, takes that.
+static size_t footprint(const Server* S, const mlb_matrix* A, const mlb_options* opt, bool& lean) {
+  const size_t fp = workspace_bytes(A, opt, false);
+  lean = opt->precond == MLB_PRECOND_ILU0 && fp > S->budget && workspace_bytes(A, opt, true) <= S->budget;
+  return lean ? workspace_bytes(A, opt, true) : fp;
 }
 
 // Whether a request of the worker queue may start now (its footprint fits; a
@@ -2913,10 +2943,7 @@ int mlb_server_submit(mlb_server_handle S, const mlb_matrix* A, const mlb_option
     r->x = x;
     r->Q = Q;
     r->ldq = ldq;
-    size_t fp = 0;
-    int rc = mlbicgstab_workspace_size(A, opt, &fp);
-    if (rc != 0) throw Error{rc, g_last_error};
-    r->footprint = fp;
+    const size_t fp = r->footprint = footprint(S, A, opt, r->lean);
     if (fp > S->budget) throw Error{MLB_ENOMEM, "request footprint exceeds the server's HBM budget"};
     {
       std::lock_guard<std::mutex> lk(S->mu);
@@ -2961,9 +2988,8 @@ int mlb_server_submit_sequence(mlb_server_handle S, uint64_t key, const mlb_matr
     if (ldq < A->nrows) throw Error{MLB_EINVAL, "ldq must be >= N"};
     mlb_options o = *opt;
     o.n = n_max;
-    size_t fp = 0;
-    int rc = mlbicgstab_workspace_size(A, &o, &fp);
-    if (rc != 0) throw Error{rc, g_last_error};
+    bool lean = false;
+    const size_t fp = footprint(S, A, &o, lean);
     if (fp > S->budget) throw Error{MLB_ENOMEM, "the sequence's footprint exceeds the server's HBM budget"};
     auto r = std::make_shared<Request>();
     r->A = *A;
@@ -2987,6 +3013,7 @@ int mlb_server_submit_sequence(mlb_server_handle S, uint64_t key, const mlb_matr
         q->step = step;
         q->n_next = opt->n;
         q->footprint = fp;
+        q->lean = lean;
         S->seqs[key] = q;
       } else {
         q = it->second;
