@@ -786,6 +786,7 @@ struct GridGate {
   GridGate(const GridGate&) = delete;
   GridGate& operator=(const GridGate&) = delete;
 };
+constexpr int SERVED_WHOLE_ROWS = 180000;   // of a server worker's request (Engine::pick_grid)
 constexpr int GRID_STARTS = 20;   // starts of a launch whose groups left at their gate
 
 // ------------------------------------------------------------------ engine
@@ -960,13 +961,15 @@ struct Engine {
     // launches / whole with 4 threads: 1.63 / 2.23 at 103,823 rows, 3.4 / 4.8 at 250,047, 6.7 /
     // 9.1 at 512,000 (fp32 2.7 / 3.8, 4.5 / 7.2, 8.5 / 12.7), where one alone takes 4.6 / 2.3,
     // 7.5 / 4.8, 12.3 / 9.1; 1.2 / 0.95 at 64,000 rows, where two groups fit.  A server worker
-    // (it lends the flag) mixes sizes, and groups of up to GRID_MAX_P - 1 slices, 130,560 rows,
-    // fill what the other requests leave: 800 requests of 1e3 to 5e5 rows, 8 at a time, solves/s
-    // 291 (fp32 refinement 171) against 293 (149) with the line at half the CUs and 258 (134)
-    // without any whole solves.  The stream alone decides, not what runs on others, so
-    // a solve's result does not depend on that.
-    const int room = s == nullptr || s == hipStreamLegacy ? GRID_MAX_P : own_flag ? device_cus() / 2 : GRID_MAX_P - 1;
-    grid_solo = P <= room && rows_suit_grid();
+    // (it lends the flag) mixes sizes, and there groups that fill what the other requests leave
+    // pay up to SERVED_WHOLE_ROWS.  800 requests of 1e3 to 5e5 rows, 8 at a time, solves/s (fp32
+    // refinement), and ms for 24 of up to 3e5 rows at once, by the line: 65,536 rows 305 (169)
+    // and 63.0, 130,560 304 (175) and 60.4, 180,000 300 (169) and 57.3, 262,144 291 (154) and
+    // 57.3, 350,000 266 (142) and 57.4, none 234 (126) and 57.1; all by launches 268 (140) and
+    // 64.  The stream alone decides, not what runs on others, so a solve's result does not
+    // depend on that.
+    const bool alone = s == nullptr || s == hipStreamLegacy;
+    grid_solo = (alone || (own_flag ? P <= device_cus() / 2 : N <= SERVED_WHOLE_ROWS)) && rows_suit_grid();
     // test hooks, read from the environment: a wait that gives up after so many tries (its solve
     // fails with MLB_EHIP), and the time a group waits at its gate (0: it mostly leaves)
     if (const char* e = std::getenv("MLB_GRID_MAX_TRIES")) {

@@ -25,14 +25,15 @@ def serve(m, precision=0):
 
 @pytest.mark.parametrize("precision", [binding.MLB_PREC_FP64, binding.MLB_PREC_FP32_IR])
 def test_large_requests_go_by_launches(precision, monkeypatch):
-    """131,044 rows: a group of 256 slices would hold the card alone."""
+    """180,625 rows, beyond the line at 180,000: a group that would hold the card alone."""
     monkeypatch.setenv("MLB_GRID_MAX_TRIES", "1")
-    assert serve(362, precision).flag == 0
+    assert serve(425, precision).flag == 0
 
 
-def test_small_requests_go_in_one_launch(monkeypatch):
-    """40,000 rows, beyond the batchers' sizes: 79 slices."""
+@pytest.mark.parametrize("m", [200, 424])
+def test_small_requests_go_in_one_launch(m, monkeypatch):
+    """40,000 rows, beyond the batchers' sizes, and 179,776, before the line."""
     monkeypatch.setenv("MLB_GRID_MAX_TRIES", "1")
     with pytest.raises(binding.MlbError) as e:
-        serve(200)
+        serve(m)
     assert e.value.code == binding.MLB_EHIP
