@@ -919,8 +919,8 @@ struct Engine {
   }
 
   // A whole solve walks a row with one lane, the multi-launch products one of more than 8
-  // entries with 16 or 32, so solve() takes the launches where a lane has much to walk.  us an
-  // iteration, launches / whole, random patterns, n = 4: entries a lane walks in a product
+  // entries with 16 or 32, so solve() takes the launches where rows are longer than that (3x3
+  // blocks: in any case) and a lane has much to walk.  us an iteration, launches / whole, random patterns, n = 4: entries a lane walks in a product
   // (a row's times rows a lane) 40: 104 / 87 (130,000 rows), 46: 112 / 97 (500,000), 48: 98 / 104
   // (260,000), 62: 131 / 137 (500,000); complex 24: 91 / 85 (260,000), 32: 101 / 107, 35: 140 /
   // 139 (500,000), 46: 162 / 175; fp32 62: 154 / 127 (500,000), 80: 173 / 217 (260,000), 93: 198 /
@@ -931,7 +931,15 @@ struct Engine {
   bool rows_suit_grid() const {
     const bool blocks = A.format == MLB_BSR3;
     const double row = (double)A.nnz / A.nbrows, walk = row * std::max(1.0, (double)grid_R / GB);
-    const double most = blocks ? (sizeof(V) > 8 ? 16 : 27) : sizeof(V) > 8 ? 31 : sizeof(V) > 4 ? 47 : row > 12 ? 64 : 96;
+    double most;   // entries a lane may walk
+    if (blocks) most = sizeof(V) > 8 ? 16 : 27;
+    else if (row <= 8) most = 8.0 * GRID_MAX_P;
+    else if (sizeof(V) > 4) most = sizeof(V) > 8 ? 31 : 47;
+    else most = row > 12 ? 64 : 96;
+    // Complex values with more than 16 shadow vectors do not fit the registers.  n = 17: 47 / 54 us
+    // at 1,000 rows, 51 / 57 at 8,000, 128 / 139 at 250,047, 188 / 257 at 512,000; but 67 / 60 at
+    // 29,791, 86 / 71 at 91,125, 105 / 88 at 140,608.
+    if (sizeof(V) > 8 && nb > 16 && (grid_P < 48 || grid_R > 640)) return false;
     return walk <= most && A.longest <= (blocks ? 48 : 96) && (long long)AH.longest * (n - 1) <= 4096;
   }
   bool grid_kr() const { return grid_R <= GB && grid_keeps_rows<V>(nb); }

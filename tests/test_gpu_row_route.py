@@ -54,6 +54,9 @@ def one_row(length, transpose=False, blocks=False):
 CASES = {   # matrix, n, solved by launches
     "47_a_row": (lambda: even(47), 4, False),
     "48_a_row": (lambda: even(48), 4, True),
+    "8_a_row": (lambda: even(8), 4, False),
+    "complex_16_shadow_vectors": (lambda: even(5, cplx=True), 16, False),
+    "complex_17_shadow_vectors": (lambda: even(5, cplx=True), 17, True),
     "complex_31": (lambda: even(31, cplx=True), 4, False),
     "complex_32": (lambda: even(32, cplx=True), 4, True),
     "blocks_27": (lambda: even(27, blocks=True), 4, False),
