@@ -164,8 +164,9 @@ __global__ void k_validate(const int* __restrict__ rp, const int* __restrict__ c
   }
 }
 
+// mapped: pinned, host-mapped memory for the longest row's length (NULL: copied).
 template <class V>
-static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s) {
+static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s, int* mapped = nullptr) {
   Mat<V> T;
   T.format = A.format;
   T.nrows = A.nrows;
@@ -204,9 +205,16 @@ static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s) {
     k_scatter<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(A.rp, A.ci, A.val, m, rpT, fill, ciT, valT);
     k_sort_rows<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT, longest);
   }
+  if (mapped) {
+    int* dev = nullptr;
+    HIP_TRY(hipHostGetDevicePointer((void**)&dev, mapped, 0));
+    k_publish<<<1, 1, 0, s>>>(longest, dev);
+  } else {
+    HIP_TRY(hipMemcpyAsync(&T.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
+  }
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(&T.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));   // tmp_own is freed on return
+  if (mapped) T.longest = *(volatile int*)mapped;
   T.rp = rpT;
   T.ci = ciT;
   T.val = valT;
@@ -837,6 +845,12 @@ struct Engine {
   unsigned grid_max_tries = ~0u;
   long long grid_entry_ticks = GRID_ENTRY_TICKS;
 
+  // The done flag, before init() too, where it may carry other words to the host.
+  int* alloc_flag() {
+    if (!host_done) HIP_TRY(hipHostMalloc((void**)&host_done, sizeof(int), hipHostMallocMapped));
+    return host_done;
+  }
+
   // ext_flag: a pinned, host-mapped int the caller owns (serving workers reuse one
   // per worker); NULL = allocate one.
   // n_alloc: the largest n this engine will run (its workspace); the active n is
@@ -860,11 +874,8 @@ struct Engine {
     own_flag = ext_flag == nullptr;   // set_n's routes depend on it
     set_n(n_alloc);
     if (poll) return;   // no host-mapped flag, no events
-    if (ext_flag) {
-      host_done = ext_flag;
-    } else {
-      HIP_TRY(hipHostMalloc((void**)&host_done, sizeof(int), hipHostMallocMapped));
-    }
+    if (ext_flag) host_done = ext_flag;
+    else alloc_flag();
     *host_done = 0;
     HIP_TRY(hipHostGetDevicePointer((void**)&host_done_dev, host_done, 0));
     for (auto& e : ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -1616,7 +1627,9 @@ static void create_impl(mlb_solver* h, const mlb_matrix* Adesc, Impl<V64, V32>& 
     im.e64.ilu = &im.ilu;
   }
   const bool tf = h->opt.transpose_free != 0;
-  const Mat<V64> AH = tf ? Mat<V64>{} : build_transpose(A, h->al, h->s);
+  int* mapped = nullptr;
+  if (!tf && !h->noalloc) mapped = h->ext_flags ? h->ext_flags : im.e64.alloc_flag();
+  const Mat<V64> AH = tf ? Mat<V64>{} : build_transpose(A, h->al, h->s, mapped);
   im.e64.tf = tf;
   im.e64.literal = h->opt.order == MLB_ORDER_LITERAL;
   im.e64.poll = h->noalloc;
