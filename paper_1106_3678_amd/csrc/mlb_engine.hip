@@ -145,10 +145,28 @@ static int pick_lpr(long long nnz, int nbrows) {
   return 32;
 }
 
+// The longest of the workgroups' lengths so far into *longest: one atomic for a workgroup that
+// has a longer one (one a wave took 20 us at 64,000 rows).
+__device__ inline void note_longest(int len, int* longest) {
+  __shared__ int most;
+  if (threadIdx.x == 0) most = 0;
+  __syncthreads();
+  for (int d = WAVE / 2; d > 0; d /= 2) len = max(len, __shfl_xor(len, d, WAVE));
+  if (threadIdx.x % WAVE == 0) atomicMax(&most, len);
+  __syncthreads();
+  if (threadIdx.x == 0 && most > *(volatile int*)longest) atomicMax(longest, most);
+}
+__global__ void k_longest(const int* __restrict__ cnt, int m, int* __restrict__ longest) {
+  int len = 0;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < m; t += gridDim.x * blockDim.x) len = max(len, cnt[t]);
+  note_longest(len, longest);
+}
+
 // Checks row_ptr / col_idx of a user matrix on the device (so that no kernel
-// ever indexes outside the arrays the descriptor declares), and finds its longest row.
+// ever indexes outside the arrays the descriptor declares), finds its longest row and
+// counts the entries of its columns (col_count, zero before; NULL: not).
 __global__ void k_validate(const int* __restrict__ rp, const int* __restrict__ ci, int nbrows, long long nnz,
-                           int ncols, int* __restrict__ bad, int* __restrict__ longest) {
+                           int ncols, int* __restrict__ bad, int* __restrict__ longest, int* __restrict__ col_count) {
   int len = 0;
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t <= nbrows; t += (long long)gridDim.x * blockDim.x) {
     const int v = rp[t];
@@ -161,12 +179,13 @@ __global__ void k_validate(const int* __restrict__ rp, const int* __restrict__ c
   for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < nnz; q += (long long)gridDim.x * blockDim.x) {
     const int c = ci[q];
     if (c < 0 || c >= ncols) atomicOr(bad, 8);
+    else if (col_count) atomicAdd(&col_count[c], 1);
   }
 }
 
-// mapped: pinned, host-mapped memory for the longest row's length (NULL: copied).
+// col_count: the entries of A's columns, used up here (NULL: counted here).
 template <class V>
-static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s, int* mapped = nullptr) {
+static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s, int* col_count = nullptr) {
   Mat<V> T;
   T.format = A.format;
   T.nrows = A.nrows;
@@ -179,16 +198,17 @@ static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s, int* m
   V* valT = al.get<V>((size_t)A.nnz * bs);
   Allocs tmp_own(al.stream, al.ordered);
   Allocs& tmp = al.arena ? al : tmp_own;   // arena mode: temporaries stay in the arena
-  int* cnt = tmp.get<int>(m);
+  int* cnt = col_count ? col_count : tmp.get<int>(m);
   int* fill = tmp.get<int>(m);
-  if (al.arena) {
-    k_fill<int><<<grid_for(m, 4096), BLOCK, 0, s>>>(cnt, m, 0);
-    k_fill<int><<<grid_for(m, 4096), BLOCK, 0, s>>>(fill, m, 0);
-  } else {
-    HIP_TRY(hipMemsetAsync(cnt, 0, sizeof(int) * m, s));
-    HIP_TRY(hipMemsetAsync(fill, 0, sizeof(int) * m, s));
+  auto clear = [&](int* p) {
+    if (al.arena) k_fill<int><<<grid_for(m, 4096), BLOCK, 0, s>>>(p, m, 0);
+    else HIP_TRY(hipMemsetAsync(p, 0, sizeof(int) * m, s));
+  };
+  clear(fill);
+  if (!col_count) {
+    clear(cnt);
+    if (A.nnz > 0) k_col_count<<<grid_for(A.nnz, 4096), BLOCK, 0, s>>>(A.ci, A.nnz, cnt);
   }
-  if (A.nnz > 0) k_col_count<<<grid_for(A.nnz, 4096), BLOCK, 0, s>>>(A.ci, A.nnz, cnt);
   {
     const int ntiles = (int)((m + SCAN_TILE - 1) / SCAN_TILE);
     int* tsum = tmp.get<int>((size_t)ntiles + 1);
@@ -196,25 +216,15 @@ static Mat<V> build_transpose(const Mat<V>& A, Allocs& al, hipStream_t s, int* m
     k_scan_sums<<<1, SCAN_T, 0, s>>>(tsum, ntiles);
     k_scan_apply<<<ntiles, SCAN_T, 0, s>>>(cnt, m, tsum, ntiles, rpT);
   }
-  int* longest = cnt;   // the counts are used up
-  k_fill<int><<<1, BLOCK, 0, s>>>(longest, 1, 0);
   if (bs == 1) {
     k_scatter<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(A.rp, A.ci, A.val, m, rpT, fill, ciT, valT);
-    k_sort_rows<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT, longest);
+    k_sort_rows<V, 1><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT);
   } else {
     k_scatter<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(A.rp, A.ci, A.val, m, rpT, fill, ciT, valT);
-    k_sort_rows<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT, longest);
-  }
-  if (mapped) {
-    int* dev = nullptr;
-    HIP_TRY(hipHostGetDevicePointer((void**)&dev, mapped, 0));
-    k_publish<<<1, 1, 0, s>>>(longest, dev);
-  } else {
-    HIP_TRY(hipMemcpyAsync(&T.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
+    k_sort_rows<V, 9><<<grid_for(m, 4096), BLOCK, 0, s>>>(rpT, m, ciT, valT);
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));   // tmp_own is freed on return
-  if (mapped) T.longest = *(volatile int*)mapped;
   T.rp = rpT;
   T.ci = ciT;
   T.val = valT;
@@ -845,12 +855,6 @@ struct Engine {
   unsigned grid_max_tries = ~0u;
   long long grid_entry_ticks = GRID_ENTRY_TICKS;
 
-  // The done flag, before init() too, where it may carry other words to the host.
-  int* alloc_flag() {
-    if (!host_done) HIP_TRY(hipHostMalloc((void**)&host_done, sizeof(int), hipHostMallocMapped));
-    return host_done;
-  }
-
   // ext_flag: a pinned, host-mapped int the caller owns (serving workers reuse one
   // per worker); NULL = allocate one.
   // n_alloc: the largest n this engine will run (its workspace); the active n is
@@ -874,8 +878,11 @@ struct Engine {
     own_flag = ext_flag == nullptr;   // set_n's routes depend on it
     set_n(n_alloc);
     if (poll) return;   // no host-mapped flag, no events
-    if (ext_flag) host_done = ext_flag;
-    else alloc_flag();
+    if (ext_flag) {
+      host_done = ext_flag;
+    } else {
+      HIP_TRY(hipHostMalloc((void**)&host_done, sizeof(int), hipHostMallocMapped));
+    }
     *host_done = 0;
     HIP_TRY(hipHostGetDevicePointer((void**)&host_done_dev, host_done, 0));
     for (auto& e : ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -1508,7 +1515,10 @@ struct mlb_solver {
   int* ext_flags = nullptr;   // two pinned host-mapped ints owned by a serving worker, or NULL
   bool noalloc = false;       // everything in the caller's arena, no host-mapped flags or events
   int n_active = 0;           // shadow vectors of the next solve (<= opt.n, the workspace's)
-  int longest = 0;            // entries of A's longest (block) row
+  int longest = 0, longest_col = 0;   // entries of A's longest (block) row and column
+  // While it is created: entries of A's columns (device; not if transpose-free), and their memory.
+  int* col_count = nullptr;
+  std::unique_ptr<Allocs> col_al;
   bool lean_ilu = false;      // ILU(0) in less memory (build_ilu)
   Allocs al;
   std::unique_ptr<Impl<double, float>> real;
@@ -1627,9 +1637,13 @@ static void create_impl(mlb_solver* h, const mlb_matrix* Adesc, Impl<V64, V32>& 
     im.e64.ilu = &im.ilu;
   }
   const bool tf = h->opt.transpose_free != 0;
-  int* mapped = nullptr;
-  if (!tf && !h->noalloc) mapped = h->ext_flags ? h->ext_flags : im.e64.alloc_flag();
-  const Mat<V64> AH = tf ? Mat<V64>{} : build_transpose(A, h->al, h->s, mapped);
+  Mat<V64> AH;
+  if (!tf) {
+    AH = build_transpose(A, h->al, h->s, h->col_count);
+    AH.longest = h->longest_col;
+  }
+  h->col_count = nullptr;
+  h->col_al.reset();   // before the workspace is taken
   im.e64.tf = tf;
   im.e64.literal = h->opt.order == MLB_ORDER_LITERAL;
   im.e64.poll = h->noalloc;
@@ -1976,19 +1990,25 @@ static std::unique_ptr<mlb_solver> create_once(const mlb_matrix* A, const mlb_op
   h->noalloc = arena != nullptr;
   // validate the index arrays on the device before any kernel relies on them
   {
-    Allocs tmp_own(stream, ordered);
-    Allocs& tmp = h->noalloc ? h->al : tmp_own;
-    int* bad = tmp.get<int>(2);   // what is wrong, entries of the longest row
-    k_fill<int><<<1, BLOCK, 0, h->s>>>(bad, 2, 0);
+    h->col_al = std::make_unique<Allocs>(stream, ordered);
+    Allocs& tmp = h->noalloc ? h->al : *h->col_al;
+    int* bad = tmp.get<int>(3);   // what is wrong, entries of the longest row and column
+    k_fill<int><<<1, BLOCK, 0, h->s>>>(bad, 3, 0);
     const int nbr = A->format == MLB_BSR3 ? (int)(A->nrows / 3) : (int)A->nrows;
-    k_validate<<<grid_for(std::max<long long>(nbr + 1, A->nnz), 4096), BLOCK, 0, h->s>>>(A->row_ptr, A->col_idx, nbr,
-                                                                                         A->nnz, nbr, bad, bad + 1);
+    if (!opt->transpose_free) {
+      h->col_count = tmp.get<int>(nbr);
+      k_fill<int><<<grid_for(nbr, 4096), BLOCK, 0, h->s>>>(h->col_count, nbr, 0);
+    }
+    k_validate<<<grid_for(std::max<long long>(nbr + 1, A->nnz), 4096), BLOCK, 0, h->s>>>(
+        A->row_ptr, A->col_idx, nbr, A->nnz, nbr, bad, bad + 1, h->col_count);
+    if (h->col_count) k_longest<<<grid_for(nbr, 4096), BLOCK, 0, h->s>>>(h->col_count, nbr, bad + 2);
     HIP_TRY(hipGetLastError());
-    int seen[2] = {0, 0};
+    int seen[3] = {0, 0, 0};
     HIP_TRY(hipMemcpyAsync(seen, bad, sizeof(seen), hipMemcpyDeviceToHost, h->s));
     HIP_TRY(hipStreamSynchronize(h->s));
     const int hb = seen[0];
     h->longest = seen[1];
+    h->longest_col = seen[2];
     if (hb) {
       std::string why;
       if (hb & 1) why += " row_ptr[0] != 0;";
@@ -2434,7 +2454,7 @@ static size_t noalloc_bytes_t(const mlb_matrix* A, const mlb_options* opt) {
   const size_t bs = bsr ? 9 : 1;
   const size_t nnz = (size_t)A->nnz;
   const bool tf = opt->transpose_free != 0;
-  size_t t = arena_bytes<int>(2);                                   // index check flag, longest row
+  size_t t = arena_bytes<int>(3);                                   // index check flag, longest row and column
   if (nnz == 0) t += arena_bytes<int>(1) + arena_bytes<V>(bs);       // stand-in index / value arrays
   if (!tf) {
     t += arena_bytes<int>(m + 1) + arena_bytes<int>(nnz) + arena_bytes<V>(nnz * bs);   // A^H

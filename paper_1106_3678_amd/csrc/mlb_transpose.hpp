@@ -120,28 +120,11 @@ __global__ void k_scatter(const int* __restrict__ rp, const int* __restrict__ ci
   }
 }
 
-// The entries of the longest row so far into *longest, by every thread of a workgroup: one
-// atomic for a workgroup that has more (one a wave took 20 us at 64,000 rows).
-__device__ inline void note_longest(int len, int* longest) {
-  __shared__ int most;
-  if (threadIdx.x == 0) most = 0;
-  __syncthreads();
-  for (int d = WAVE / 2; d > 0; d /= 2) len = max(len, __shfl_xor(len, d, WAVE));
-  if (threadIdx.x % WAVE == 0) atomicMax(&most, len);
-  __syncthreads();
-  if (threadIdx.x == 0 && most > *(volatile int*)longest) atomicMax(longest, most);
-}
-// Into host-mapped memory: a copy to the host takes 28 us, a fifth of a small create().
-__global__ void k_publish(const int* from, int* to) { *(volatile int*)to = *from; }
-
 // Sort every row of A^H by column (insertion sort; rows are short).
 template <class V, int BS>
-__global__ void k_sort_rows(const int* __restrict__ rpT, int nrows, int* __restrict__ ciT, V* __restrict__ valT,
-                            int* __restrict__ longest = nullptr) {
-  int len = 0;
+__global__ void k_sort_rows(const int* __restrict__ rpT, int nrows, int* __restrict__ ciT, V* __restrict__ valT) {
   for (int row = blockIdx.x * blockDim.x + threadIdx.x; row < nrows; row += gridDim.x * blockDim.x) {
     const int beg = rpT[row], end = rpT[row + 1];
-    len = max(len, end - beg);
     for (int a = beg + 1; a < end; ++a) {
       const int key = ciT[a];
       V tmp[BS];
@@ -159,7 +142,6 @@ __global__ void k_sort_rows(const int* __restrict__ rpT, int nrows, int* __restr
       for (int e = 0; e < BS; ++e) valT[(size_t)BS * (b + 1) + e] = tmp[e];
     }
   }
-  if (longest) note_longest(len, longest);
 }
 
 // Narrowing copy of matrix values (fp64 -> fp32) for the fp32 inner iteration.
